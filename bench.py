@@ -440,9 +440,11 @@ def step_stats(ms) -> dict:
 
 
 def kernel_source_digest() -> str:
-    path = os.path.join(ROOT, "paper_2607_27692_amd", "csrc", "retopk_kernels.hip")
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for name in ("retopk_kernels.hip", "retopk_device.h"):
+        with open(os.path.join(ROOT, "paper_2607_27692_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def traffic_per_launch(kernel: str, workload: str):
@@ -968,7 +970,9 @@ SYMBOLS = {  # kernel symbol prefix -> name used by the library's own profiling
     "void retopk::k_final<": "retopk_final",
     "void retopk::k_dense<": "dense_chunk",
     "void retopk::k_dense_merge<": "dense_merge",
-    "void retopk::k_pf_score<": "prefill_score",
+    "void retopk::k_pf_scan<": "prefill_score",
+    "void retopk::k_pf_bound<": "retopk_filter",
+    "void retopk::k_pf_select<": "retopk_final",
     "void retopk::k_scan_list<": "retopk_scan",
 }
 
@@ -991,9 +995,11 @@ def _read_csv(path):
 
 def _passes(names, w, steps, warmup):
     """Splits the library's dispatches (in dispatch order) into the bench's
-    passes.  Every pass starts on a fresh handle whose prefill issues a
-    prefill_score, filter, final triple per launch of prompt-tail positions (a
-    scan, filter, final triple per position for f32); a decode step that selects
+    passes.  Every pass starts on a fresh handle whose prefill issues, per launch
+    of prompt-tail positions, prefill_score, filter, prefill_score, final (bounds
+    and lists) or prefill_score, final (score rows), or the older prefill_score,
+    filter, final triple (a scan, filter, final triple per position for f32); a
+    decode step that selects
     issues sim, score, filter, final, any other step or an Exact Top-K step
     scan, filter, final, and a full-attention step dense_chunk, dense_merge.
     The warm-up runs one step of each kind per warm-up step, then one handle
@@ -1009,19 +1015,22 @@ def _passes(names, w, steps, warmup):
              "retopk_scan": ["retopk_scan", "retopk_filter", "retopk_final"],
              "dense_chunk": ["dense_chunk", "dense_merge"]}
     out, i = [], 0
-    pf = ["prefill_score", "retopk_filter", "retopk_final"]
+    pf_units = (["prefill_score", "retopk_filter", "prefill_score", "retopk_final"],
+                ["prefill_score", "retopk_filter", "retopk_final"],
+                ["prefill_score", "retopk_final"])
     prefill = None
-    n_pf = None      # triples per prefill: every handle's prefill is the same
+    pf = None        # one prefill's launches: every handle's prefill is the same
     for label, n_units in plan:
         p0 = i
         if names[i] == "prefill_score":
-            if n_pf is None:   # the first handle's prefill is followed by steps
-                n_pf = 0
-                while names[i + 3 * n_pf:i + 3 * n_pf + 3] == pf:
-                    n_pf += 1
-            for _ in range(n_pf):
-                assert names[i:i + 3] == pf, f"unexpected prefill at {i}"
-                i += 3
+            if pf is None:     # the first handle's prefill is followed by steps
+                pf, j = [], i
+                while names[j] == "prefill_score":
+                    unit = next(u for u in pf_units if names[j:j + len(u)] == u)
+                    pf += unit
+                    j += len(unit)
+            assert names[i:i + len(pf)] == pf, f"unexpected prefill at {i}"
+            i += len(pf)
         else:
             for _ in range(w.cache_cap):
                 assert names[i:i + 3] == units["retopk_scan"], f"unexpected prefill at {i}"

@@ -10,6 +10,7 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 using namespace retopk;
@@ -18,9 +19,12 @@ namespace {
 
 constexpr int kProfileMaxLaunches = 65536;
 constexpr int kNumKernels = 8;
-// Temporary device memory one batched prefill launch sequence may use (scores,
-// survivors and histograms of U positions of every head).
-constexpr size_t kPfWorkspaceBytes = (size_t)2 << 30;
+// Device memory of the batched prefill (the lists or score rows of U positions of
+// every head), allocated by the handle's first prefill and kept: allocating it per
+// call cost 0.45 ms of an 8.9 ms prefill at 128K, and 17 ms where other handles'
+// memory came and went between the calls.  256 MiB hold 256 positions of 32 heads at
+// K = 512 (32 KiB of list a virtual head and 8 bytes beside it), past which the key reads per launch are no longer what bounds it.
+constexpr size_t kPfWorkspaceBytes = (size_t)257 << 20;
 // retopk_score is the scoring kernel of a decode step that selects (candidate
 // blocks beside the scans of fallback heads); retopk_scan is the same kernel
 // built for steps where every head takes the full-history scan.
@@ -47,6 +51,8 @@ struct retopk_handle_s {
     hipStream_t last_stream = nullptr;
     bool has_last = false;             // a call has queued work on last_stream
     hipEvent_t order_ev = nullptr;     // orders a call on a new stream after the last
+    void *pf_mem = nullptr;            // batched prefill workspace
+    size_t pf_bytes = 0;
     // host-side counters (paths decided on the host)
     uint64_t steps = 0, head_steps = 0, refresh = 0, cold = 0, host_scans = 0;
     // profiling
@@ -101,7 +107,6 @@ StepArgs config_args(const retopk_config &c)
     a.retrieval = c.retrieval;
     a.inv_sqrt_d = (float)(1.0 / std::sqrt((double)c.head_dim));
     a.q_head_stride = c.head_dim;
-    a.U = 1;
     return a;
 }
 
@@ -256,82 +261,183 @@ retopk_status run_step(retopk_handle h, const StepArgs &a, int mode, hipStream_t
     return RETOPK_OK;
 }
 
+// Grid of k_pf_scan for `cols` virtual queries per KV group over the rows of
+// `groups` KV groups: as many waves side by side along the queries as there are
+// 128-query tiles (up to the block's 8), and key chunks for about one block per CU
+// (a CU holds one, by its registers; each block first loads its queries, 256 KB, so
+// two shorter blocks one after the other cost 4 % more), no shorter than 512 rows.
+void prefill_grid(PfArgs &p, int64_t cols, int64_t groups, int64_t rows)
+{
+    const int64_t tiles = ceil_div(cols, kPfWaveCols);
+    p.wc = 1;
+    while (p.wc < kPfThreads / 64 && p.wc < tiles) p.wc *= 2;
+    p.col_blocks = (int)ceil_div(tiles, p.wc);
+    const int64_t want = ceil_div(kCUs, groups * p.col_blocks);
+    const int64_t most = ceil_div(rows, 512);
+    const int64_t n = want < most ? want : most;
+    const int64_t unit = 16 * (kPfThreads / 64 / p.wc);
+    p.chunk_rows = ceil_div(ceil_div(rows, n), unit) * unit;
+    p.chunks = (int)ceil_div(rows, p.chunk_rows);
+    p.pairs = (int)(groups * p.chunks);
+}
+
 // Batched prefill initialisation (bf16): positions u_first .. n-1 of q_tail in
-// launches of U positions each, every launch scoring its U x B x Hq virtual
-// heads on the matrix cores (k_pf_score) and selecting and inserting them with
-// k_filter and k_final, on temporary workspaces.  Returns RETOPK_ERR_OOM, having
-// launched nothing, when the workspaces cannot be allocated.
+// launch sequences of U positions each (see retopk_prefill.hip).  A launch whose
+// shortest prefix is at least `cap` rows long collects lists under a bound of the
+// K-th largest score; a shorter one stores its score rows.  Positions in which a
+// list overflowed are run again with score rows.  Returns RETOPK_ERR_OOM, having
+// launched nothing, when the workspace cannot be allocated.
 retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, int32_t u_first,
-                              const void *k, const void *v, int64_t prefill_len, hipStream_t s)
+                              const void *k, int64_t prefill_len, hipStream_t s)
 {
     const retopk_config &c = h->cfg;
-    const int64_t BH = heads_of(c);
-    StepArgs a = base_args(h);
-    const int64_t NR = a.n_regions, RS = a.row_stride;
-    const size_t per_u = (size_t)BH * ((size_t)RS * (8 + 4) + (size_t)NR * 4 + (size_t)kHistBins * 4);
-    const int32_t n_eff = n - u_first;
-    int64_t U = (int64_t)(kPfWorkspaceBytes / per_u);
-    // whole query tiles where the budget allows: U a multiple of kPfCols / gcd(G, kPfCols)
-    int gcd = h->G, m = kPfCols;
+    const int64_t BH = heads_of(c), C = c.cache_cap, K = c.k;
+    const int64_t n_eff = n - u_first, groups = (int64_t)c.batch * c.n_kv_heads;
+    const size_t es = elem_size(c);
+    // List capacity: eight times K, four times what the bound is expected to leave.
+    const int64_t cap = 8 * K > kPfMinList ? 8 * K : kPfMinList;
+    const int64_t rows16 = ceil_div(prefill_len, 16) * 16;
+    // Bytes per virtual head: a list of cap ranks, which also holds its group maxima
+    // (at most 8 K floats) or a score row of up to 2 cap rows; its count and bound.
+    const int64_t row_bytes = rows16 * 4 < cap * 8 ? rows16 * 4 : cap * 8;
+    const int64_t per_u = BH * (row_bytes + 8);
+    int64_t U = (int64_t)kPfWorkspaceBytes / per_u;
+    // whole 128-query tiles where the budget allows
+    int gcd = h->G, m = kPfWaveCols;
     while (m) {
         const int r = gcd % m;
         gcd = m;
         m = r;
     }
-    const int64_t step = kPfCols / gcd;
-    if (U >= step) U -= U % step;
+    const int64_t unit = kPfWaveCols / gcd;
+    if (U >= unit) U -= U % unit;
     U = U < 1 ? 1 : (U > n_eff ? n_eff : U);
-    void *mem = nullptr;
-    if (hipMalloc(&mem, per_u * (size_t)U + 1024) != hipSuccess) {
-        (void)hipGetLastError();
-        return RETOPK_ERR_OOM;
-    }
-    Ws w = h->w;
-    char *p = (char *)mem;
-    w.surv = (uint64_t *)p;
-    p += (size_t)U * BH * RS * 8;
-    w.scores = (float *)p;
-    p += (size_t)U * BH * RS * 4;
-    w.hist = (uint32_t *)p;
-    p += (size_t)U * BH * kHistBins * 4;
-    w.surv_cnt = (uint32_t *)p;
-    retopk_status st = RETOPK_OK;
-    if (hipMemsetAsync(w.hist, 0, (size_t)U * BH * kHistBins * 4, s) != hipSuccess) st = fail(h);
-    const size_t es = elem_size(c);
-    for (int32_t u0 = u_first; u0 < n && st == RETOPK_OK; u0 += (int32_t)U) {
-        const int32_t Uc = (int32_t)(n - u0 < U ? n - u0 : U);
-        StepArgs b = a;
-        b.mode = MODE_PREFILL;
-        b.U = Uc;
-        b.q = q_tail + (size_t)u0 * c.head_dim * es;
-        b.q_head_stride = (int64_t)n * c.head_dim;
-        b.k = k;
-        b.v = v;
-        b.len = prefill_len - n + u0 + 1;
-        b.out = nullptr;
-        b.sel = nullptr;
-        b.n_ins = h->n_ins;
-        b.insert_slot = (int32_t)(h->n_ins % c.cache_cap);
-        b.do_insert = 1;
-        const int64_t len_max = b.len + Uc - 1;
-        Geometry geo{};
-        geo.filter_blocks_per_head = (int)ceil_div(len_max, kFilterRows);
-        geo.pf_qtiles = (int)ceil_div((int64_t)h->G * Uc, kPfCols);
-        geo.pf_kchunks = (int)ceil_div(len_max, kPfKeys);
-        geo.pf_pairs = c.batch * c.n_kv_heads * geo.pf_kchunks;
-        void *args[3] = {&b, &w, &geo};
-        const int kinds[3] = {KERNEL_PF_SCORE, KERNEL_FILTER, KERNEL_FINAL};
-        const int kids[3] = {KID_PF_SCORE, KID_FILTER, KID_FINAL};
-        for (int i = 0; i < 3 && st == RETOPK_OK; ++i) {
-            KernelDesc d;
-            describe_kernel(kinds[i], c.dtype, b, geo, &d);
-            st = launch_desc(h, d, kids[i], args, s);
+    // overflow words of every position, then the virtual heads' memory
+    const size_t head = ((size_t)n_eff * 4 + 255) / 256 * 256;
+    const bool lists = row_bytes == cap * 8 && prefill_len > cap;
+    const size_t body = (size_t)(per_u * U);
+    if (h->pf_bytes < head + body) {
+        if (h->pf_mem) (void)hipFree(h->pf_mem);    // its last prefill has finished
+        h->pf_mem = nullptr;
+        h->pf_bytes = 0;
+        if (hipMalloc(&h->pf_mem, head + body) != hipSuccess) {
+            (void)hipGetLastError();
+            h->pf_mem = nullptr;
+            return RETOPK_ERR_OOM;
         }
-        h->n_ins += Uc;
+        h->pf_bytes = head + body;
     }
-    // the workspaces are released once the launches that use them are done
+    const size_t room = h->pf_bytes - head;
+    char *mem = (char *)h->pf_mem + head;
+
+    PfArgs p{};
+    p.B = c.batch;
+    p.Hq = c.n_q_heads;
+    p.Hkv = c.n_kv_heads;
+    p.G = h->G;
+    p.D = c.head_dim;
+    p.K = c.k;
+    p.M = c.cache_cap;
+    p.max_len = c.max_len;
+    p.inv_sqrt_d = h->inv_sqrt_d;
+    p.q_head_stride = (int64_t)n * c.head_dim;
+    p.k = (const uint16_t *)k;
+    p.cap = (int)cap;
+    p.qbar = h->w.qbar;
+    p.supp = h->w.supp;
+    p.supp_cnt = h->w.cnt;
+    bool any_list = false;
+    // One launch sequence: positions u0 .. u0 + Uc - 1 (relative to u_first).
+    auto sequence = [&](int64_t u0, int64_t Uc, bool dense, float *rows, int64_t stride) -> retopk_status {
+        p.U = (int)Uc;
+        p.q = (const uint16_t *)(q_tail + (size_t)(u_first + u0) * c.head_dim * es);
+        p.len0 = prefill_len - n + u_first + u0 + 1;
+        p.insert_slot = (int32_t)((h->n_ins + u0) % C);
+        p.overflow = (uint32_t *)h->pf_mem + u0;
+        const int64_t len_max = p.len0 + Uc - 1;
+        const int64_t vheads = BH * Uc;
+        prefill_grid(p, h->G * Uc, groups, len_max);
+        void *args[1] = {&p};
+        auto launch = [&](int which, int kid) -> retopk_status {
+            KernelDesc d;
+            describe_prefill(which, p, &d);
+            return launch_desc(h, d, kid, args, s);
+        };
+        retopk_status st;
+        if (dense) {
+            p.scores = rows;
+            p.score_stride = stride;
+            if ((st = launch(PF_DENSE, KID_PF_SCORE)) != RETOPK_OK) return st;
+            return launch(PF_SELECT_DENSE, KID_FINAL);
+        }
+        p.list = (uint64_t *)mem;
+        p.maxima = (float *)mem;
+        p.cnt = (uint32_t *)(mem + vheads * cap * 8);
+        p.thr = (float *)(p.cnt + vheads);
+        // Key sample of the bound: one tile in F, so that about F K = cap / 4 entries
+        // pass it, in groups of 2^lt tiles, so that there are 4 K to 8 K maxima.
+        const int64_t tiles = p.len0 / 16;
+        int64_t F = cap / (4 * K);
+        if (F > tiles / K) F = tiles / K;
+        if (F < 1) F = 1;
+        const int64_t sampled = tiles / F;
+        p.F = (int)F;
+        p.lt = 0;
+        while ((sampled >> (p.lt + 1)) >= K) ++p.lt;
+        p.n_groups = (int)(sampled >> p.lt);
+        const int64_t wk = kPfThreads / 64 / p.wc;
+        const int chunks = p.chunks, pairs = p.pairs;
+        p.chunk_groups = (int)(ceil_div(ceil_div(p.n_groups, p.chunks), wk) * wk);
+        p.chunks = (int)ceil_div(p.n_groups, p.chunk_groups);
+        p.pairs = (int)(groups * p.chunks);
+        if ((st = launch(PF_BOUND, KID_PF_SCORE)) != RETOPK_OK) return st;
+        p.chunks = chunks;
+        p.pairs = pairs;
+        if ((st = launch(PF_THRESHOLD, KID_FILTER)) != RETOPK_OK) return st;
+        if ((st = launch(PF_COLLECT, KID_PF_SCORE)) != RETOPK_OK) return st;
+        any_list = true;
+        return launch(PF_SELECT_LIST, KID_FINAL);
+    };
+    retopk_status st = RETOPK_OK;
+    std::vector<uint32_t> over((size_t)n_eff, 0u);
+    std::vector<std::pair<int64_t, int64_t>> listed;     // position ranges run with lists
+    for (int64_t u0 = 0; u0 < n_eff && st == RETOPK_OK;) {
+        const int64_t Uc = n_eff - u0 < U ? n_eff - u0 : U;
+        const bool dense = !lists || prefill_len - n + u_first + u0 + 1 < cap;
+        if (!dense) listed.emplace_back(u0, Uc);
+        // (the rows of a launch of short prefixes: fewer than cap + C <= 2 cap of them)
+        st = sequence(u0, Uc, dense, (float *)mem, row_bytes / 4);
+        u0 += Uc;
+    }
+    if (any_list && st == RETOPK_OK &&
+        hipMemcpyAsync(over.data(), h->pf_mem, (size_t)n_eff * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+        st = fail(h);
+    // the call returns once the stream has finished its work
     if (hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
-    (void)hipFree(mem);
+    // The overflowed positions again, with score rows: as many at a time as fit, or
+    // one in the handle's own score rows.
+    const int64_t fit = (int64_t)(room / ((size_t)BH * (size_t)rows16 * 4));
+    float *const rows = fit > 0 ? (float *)mem : h->w.scores;
+    const int64_t stride = fit > 0 ? rows16 : base_args(h).row_stride;
+    bool again = false;
+    for (const auto &r : listed) {
+        for (int64_t u0 = r.first; u0 < r.first + r.second && st == RETOPK_OK;) {
+            if (!over[(size_t)u0]) {
+                ++u0;
+                continue;
+            }
+            int64_t most = fit > 0 ? fit : 1;
+            if (most > r.first + r.second - u0) most = r.first + r.second - u0;
+            int64_t Uc = 1;
+            for (int64_t i = 1; i < most; ++i)
+                if (over[(size_t)(u0 + i)]) Uc = i + 1;
+            st = sequence(u0, Uc, true, rows, stride);
+            again = true;
+            u0 += Uc;
+        }
+    }
+    if (again && hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
+    h->n_ins += n_eff;
     return st;
 }
 
@@ -440,6 +546,7 @@ retopk_status retopk_destroy(retopk_handle h)
     (void)hipSetDevice(h->device);
     if (!h->allocs.empty()) (void)hipDeviceSynchronize();
     for (void *p : h->allocs) (void)hipFree(p);
+    if (h->pf_mem) (void)hipFree(h->pf_mem);
     for (hipEvent_t e : h->ev) (void)hipEventDestroy(e);
     if (h->order_ev) (void)hipEventDestroy(h->order_ev);
     delete h;
@@ -545,8 +652,7 @@ retopk_status retopk_prefill_init(retopk_handle h, const void *q_tail, int32_t n
     h->n_ins += u_first;
     set_last(h, s);
     if (c.dtype == RETOPK_BF16 && n - u_first > 1) {
-        const retopk_status st = prefill_batched(h, (const char *)q_tail, n, u_first, k, v,
-                                                 prefill_len, s);
+        const retopk_status st = prefill_batched(h, (const char *)q_tail, n, u_first, k, prefill_len, s);
         if (st != RETOPK_ERR_OOM) return st;
     }
     const size_t es = elem_size(c);

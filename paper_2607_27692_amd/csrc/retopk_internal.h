@@ -34,13 +34,10 @@ constexpr int kScanBlocksSelect = kCUs; // k_score scan blocks in MODE_SELECT (o
 constexpr int kScanBlocksExact = 2048;  // k_score scan blocks when every head is exact
 constexpr int64_t kMaxLen = (int64_t)kMaxRegions * kFilterRows;
 
-// Batched prefill initialisation (bf16): k_pf_score blocks take kPfCols virtual
-// queries (one MFMA column each) against kPfKeys keys of one KV group.
+// Batched prefill initialisation (bf16, retopk_prefill.hip).
 constexpr int kPfThreads = 512;
-constexpr int kPfCols = 32;
-constexpr int kPfKeys = 4096;
-constexpr int kPfTiles = 2;           // 16-key tiles per wave per iteration
-constexpr int kPfHistStride = kHistBins / 2 + 1;   // padded LDS histogram row (16-bit counts)
+constexpr int kPfWaveCols = 128;      // virtual queries held by one wave
+constexpr int kPfMinList = 4096;      // smallest list capacity of a virtual head
 
 // Step modes.  SELECT runs the per-head path rule on the device; the others take
 // the exact path for every head.
@@ -107,16 +104,12 @@ struct StepArgs {
     int64_t q_head_stride;
     const void *k;
     const void *v;
-    int64_t len;               // with U > 1: the length of position 0 of the launch
+    int64_t len;
     // MODE_SELECT: the split of [0, len) into the range blocks' index ranges
     // (range_split): ranges 0 .. kCandRanges-n_win-1 cover [0, w0) in spans of
     // span_old rows, the others the window [w0, len) in spans of span_win
     int64_t w0, span_old, span_win;
     int n_win;
-    int U;                     // query positions per launch: 1, or more in the batched
-                               // prefill, where virtual head vh = u * B * Hq + bh holds
-                               // position u (length len + u, q at + u * d, slot
-                               // insert_slot + u) in the workspaces
     float *out;                // nullable in MODE_PREFILL
     int32_t *sel;              // nullable
     int64_t n_ins;             // insertions before this step
@@ -138,14 +131,45 @@ struct Geometry {
     int filter_blocks_per_head;
     int list_mode;             // every KV group scanned by k_scan_list, one block per
                                // filter region: k_filter reads local survivors
-    // batched prefill (k_pf_score): (KV group, key chunk) pairs, query tiles of
-    // kPfCols virtual queries, key chunks of kPfKeys keys per group
-    int pf_pairs, pf_qtiles, pf_kchunks;
 };
 
-// One kernel of a step, ready to launch (hipLaunchKernel) or to put in a graph
-// node: the kernel takes (StepArgs, Ws) when nargs == 2 and (StepArgs, Ws,
-// Geometry) when nargs == 3, all by value.
+// One launch of the batched prefill (by value): U positions of every head, the
+// shortest prefix len0 rows long, position u's len0 + u.  Virtual head
+// vh = u * B * Hq + bh is position u of head bh; the virtual queries of a KV group
+// are vq = u * G + j.
+struct PfArgs {
+    int B, Hq, Hkv, G, D, K, M, U;
+    int64_t max_len, len0;
+    float inv_sqrt_d;
+    const uint16_t *q;         // position u of head bh at q + bh * q_head_stride + u * D
+    int64_t q_head_stride;
+    const uint16_t *k;
+    // grid of k_pf_scan: pairs = KV groups x chunks, col_blocks blocks of wc * 128
+    // virtual queries each
+    int wc, col_blocks, chunks, pairs;
+    int64_t chunk_rows;        // rows of a chunk (COLLECT, DENSE)
+    // key sample of the bound: one tile of 16 keys in F, 2^lt tiles to a group
+    int F, lt, n_groups, chunk_groups;
+    int cap;                   // list capacity of a virtual head
+    uint64_t *list;            // [U * BH, cap] ranks, in no order
+    float *maxima;             // [U * BH, 2 * cap] group maxima (the lists' memory, before them)
+    float *scores;             // DENSE: [U * BH, score_stride] score rows (the same memory)
+    int64_t score_stride;
+    uint32_t *cnt;             // [U * BH] entries appended (past cap: overflowed)
+    float *thr;                // [U * BH] lower bound of the K-th largest raw score
+    uint32_t *overflow;        // [U] set: some head of the position overflowed its list
+    // the cache
+    float *qbar;
+    int32_t *supp;
+    int32_t *supp_cnt;
+    int32_t insert_slot;       // slot of position 0
+};
+enum : int { PF_BOUND = 0, PF_COLLECT = 1, PF_DENSE = 2, PF_THRESHOLD = 3, PF_SELECT_LIST = 4,
+             PF_SELECT_DENSE = 5 };
+
+// One kernel of a step, ready to launch (hipLaunchKernel): the kernel takes
+// (StepArgs, Ws) when nargs == 2 and (StepArgs, Ws, Geometry) when nargs == 3, or
+// PfArgs when nargs == 1, all by value.
 struct KernelDesc {
     const void *func;
     dim3 grid;
@@ -154,7 +178,7 @@ struct KernelDesc {
     int nargs;
 };
 enum : int { KERNEL_SIM = 0, KERNEL_SCORE = 1, KERNEL_FILTER = 2, KERNEL_FINAL = 3,
-              KERNEL_DENSE = 4, KERNEL_DENSE_MERGE = 5, KERNEL_PF_SCORE = 6 };
+              KERNEL_DENSE = 4, KERNEL_DENSE_MERGE = 5 };
 
 // Full (dense) attention: rows per chunk block, and the chunk count for a length.
 constexpr int kDenseRows = 1024;
@@ -176,6 +200,8 @@ Geometry step_geometry(const retopk_config &c, int64_t len, int mode);
 // Fills *k for kernel `which` of a step in a.mode (retopk_kernels.hip).
 // dtype: 0 = f32, 1 = bf16.
 void describe_kernel(int which, int dtype, const StepArgs &a, const Geometry &geo, KernelDesc *k);
+// Fills *k for kernel `which` (PF_*) of a batched prefill launch (retopk_prefill.hip).
+void describe_prefill(int which, const PfArgs &a, KernelDesc *k);
 bool shape_supported(int dtype, int d, int g);
 // Streaming read of `bytes` at src (a measurement aid; retopk_stream.hip).
 void launch_stream_read(const void *src, int64_t bytes, uint32_t *sink, hipStream_t s);

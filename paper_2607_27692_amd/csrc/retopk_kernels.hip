@@ -33,340 +33,11 @@
 // lower index: every entry carries a 64-bit rank (score key << 32 | ~index), and
 // ranks are distinct.
 #include "retopk_internal.h"
+#include "retopk_device.h"
 
 #include <hip/hip_ext.h>
 
 namespace retopk {
-
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-// ---------------------------------------------------------------------------
-// Scalar helpers
-// ---------------------------------------------------------------------------
-
-// Order-preserving image of an fp32 score (finite inputs); -0.0 maps like +0.0.
-__device__ __forceinline__ uint32_t ord_key(float s)
-{
-    uint32_t u = __float_as_uint(s);
-    if (u == 0x80000000u) u = 0u;
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-__device__ __forceinline__ float key_score(uint32_t k)
-{
-    uint32_t u = (k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k;
-    return __uint_as_float(u);
-}
-
-// Larger rank = higher score, or equal score and lower index.
-__device__ __forceinline__ uint64_t rank_of(float s, uint32_t idx)
-{
-    return ((uint64_t)ord_key(s) << 32) | (uint64_t)(0xFFFFFFFFu - idx);
-}
-__device__ __forceinline__ uint32_t rank_index(uint64_t r) { return 0xFFFFFFFFu - (uint32_t)r; }
-__device__ __forceinline__ uint32_t rank_key(uint64_t r) { return (uint32_t)(r >> 32); }
-
-__device__ __forceinline__ float bf16_lo(uint32_t x) { return __uint_as_float(x << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t x) { return __uint_as_float(x & 0xFFFF0000u); }
-
-template <typename T> __device__ __forceinline__ double elem_f64(const T *p, int i);
-template <> __device__ __forceinline__ double elem_f64<float>(const float *p, int i)
-{
-    return (double)p[i];
-}
-template <> __device__ __forceinline__ double elem_f64<uint16_t>(const uint16_t *p, int i)
-{
-    return (double)__uint_as_float((uint32_t)p[i] << 16);
-}
-
-// ---------------------------------------------------------------------------
-// Cross-lane helpers (DPP inside a quad of lanes; shuffles elsewhere)
-// ---------------------------------------------------------------------------
-
-constexpr int kQuadXor1 = 0xB1;   // quad_perm:[1,0,3,2]
-constexpr int kQuadXor2 = 0x4E;   // quad_perm:[2,3,0,1]
-constexpr int kHalfMirror = 0x141; // row_half_mirror: lane i <-> 7 - i in each 8 lanes
-
-template <int CTRL> __device__ __forceinline__ float dpp_f32(float x)
-{
-    return __builtin_bit_cast(float,
-        __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-}
-
-template <int CTRL> __device__ __forceinline__ double dpp_f64(double x)
-{
-    uint64_t u = __builtin_bit_cast(uint64_t, x);
-    int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)u, CTRL, 0xF, 0xF, true);
-    int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
-    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
-}
-
-// Sum over the 4 lanes of a quad; every lane of the quad gets the same value.
-__device__ __forceinline__ float quad_sum(float x)
-{
-    x += dpp_f32<kQuadXor1>(x);
-    x += dpp_f32<kQuadXor2>(x);
-    return x;
-}
-__device__ __forceinline__ double quad_sum(double x)
-{
-    x += dpp_f64<kQuadXor1>(x);
-    x += dpp_f64<kQuadXor2>(x);
-    return x;
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave: Hillis-Steele inside each row
-// of 16 lanes (DPP row shifts, lanes shifted in from outside the row read 0), then
-// the row totals carried across rows with the row broadcasts of lanes 15 and 31.
-// Reductions over a wave: DPP inside each row of 16 lanes (quad swaps, half-row
-// and row mirrors), then the four row results read as scalars.  Every lane gets
-// the result.
-__device__ __forceinline__ uint32_t row_max_u32(uint32_t x)
-{
-    x = max(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kQuadXor1, 0xF, 0xF, true));
-    x = max(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kQuadXor2, 0xF, 0xF, true));
-    x = max(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kHalfMirror, 0xF, 0xF, true));
-    x = max(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x140, 0xF, 0xF, true));   // row_mirror
-    return x;
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
-{
-    x = row_max_u32(x);
-    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)x, 0);
-    const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)x, 16);
-    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)x, 32);
-    const uint32_t r3 = (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
-    return max(max(r0, r1), max(r2, r3));
-}
-__device__ __forceinline__ float wave_sum_f32(float x)
-{
-    x += dpp_f32<kQuadXor1>(x);
-    x += dpp_f32<kQuadXor2>(x);
-    x += dpp_f32<kHalfMirror>(x);
-    x += dpp_f32<0x140>(x);   // row_mirror
-    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 0));
-    const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16));
-    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 32));
-    const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 48));
-    return (r0 + r1) + (r2 + r3);
-}
-
-__device__ __forceinline__ double wave_max_f64(double x)
-{
-    x = fmax(x, dpp_f64<kQuadXor1>(x));
-    x = fmax(x, dpp_f64<kQuadXor2>(x));
-    x = fmax(x, dpp_f64<kHalfMirror>(x));
-    x = fmax(x, dpp_f64<0x140>(x));   // row_mirror
-    auto rl = [&](int l) {
-        const uint64_t u = __builtin_bit_cast(uint64_t, x);
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-        return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-    };
-    return fmax(fmax(rl(0), rl(16)), fmax(rl(32), rl(48)));
-}
-
-// x from lane (i + n) mod 16 of the same row of 16 lanes (DPP row_ror:n, 1..15).
-__device__ __forceinline__ float row_ror_f32(float x, int n)
-{
-    int r;
-    switch (n) {
-    case 1: r = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x121, 0xF, 0xF, true); break;
-    case 2: r = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x122, 0xF, 0xF, true); break;
-    case 4: r = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x124, 0xF, 0xF, true); break;
-    default: r = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128, 0xF, 0xF, true); break;
-    }
-    return __builtin_bit_cast(float, r);
-}
-
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);  // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);  // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);  // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
-    return x;
-}
-
-// Block reductions.  All threads must call them; every thread gets the same
-// result (fixed combination order).  red: NT/64 scratch slots.
-template <int NT, typename V, typename Op>
-__device__ __forceinline__ V block_reduce(V v, V *red, Op op)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    V t = red[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) t = op(t, red[w]);
-    __syncthreads();
-    return t;
-}
-
-// Exclusive prefix sum over the block; *total receives the block sum.
-template <int NT>
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *red, uint32_t *total)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = wave_incl_scan(v);
-    if (lane == 63) red[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        uint32_t x = red[w];
-        if (w < wave) before += x;
-        tot += x;
-    }
-    __syncthreads();
-    *total = tot;
-    return before + incl - v;
-}
-
-// ---------------------------------------------------------------------------
-// Row geometry.  A row of D elements of type T is split over the 4 lanes of a
-// quad: lane p holds the 16-byte vectors s*4 + p, s = 0 .. NV-1.  One wave covers
-// 16 rows per pass, and each load instruction reads 64 contiguous bytes per row.
-// ---------------------------------------------------------------------------
-
-template <typename T, int D> struct RowT {
-    static constexpr int kBytes = D * (int)sizeof(T);
-    static constexpr int kNV = kBytes / 64;
-    static constexpr int kEPV = 16 / (int)sizeof(T);
-};
-
-// Waves per SIMD that k_score is built for: 4 (two 512-thread blocks per CU), or
-// 2 (256 registers a lane) where the group's query vectors and the two key rows a
-// lane holds in flight would take more than 96 of 128 registers (G + 2 rows of
-// kNV * 4 in the quad layout), or, in the octet layout of the fp32 8-head build,
-// where the query vectors alone would take half of them (the bf16 8-head build
-// holds D / 32 MFMA operands).
-template <typename T, int D, int G>
-constexpr int kGroupWaves = (G == 8 && sizeof(T) == 2) ? 4
-                            : G == 8 ? (2 * G * RowT<T, D>::kNV > 64 ? 2 : 4)
-                                     : ((G + 2) * RowT<T, D>::kNV * 4 > 96 ? 2 : 4);
-// The same for k_dense, whose lanes also hold G value accumulators of kEPV floats
-// (the 8-head build takes its scores in the octet layout, its queries dead by
-// the time the accumulators live).
-template <typename T, int D, int G>
-constexpr int kDenseWaves = G == 8 ? (16 * RowT<T, D>::kNV > 64 ? 2 : 4)
-                                   : (G * (4 * RowT<T, D>::kNV + RowT<T, D>::kEPV) > 96 ? 2 : 4);
-
-template <typename T> struct Dot;
-template <> struct Dot<uint16_t> {
-    // 8 bf16 products accumulated in fp32 with v_dot2_f32_bf16.
-    static __device__ __forceinline__ float f(uint4 k, uint4 q, float acc)
-    {
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, k.x),
-                                              __builtin_bit_cast(bf16x2_t, q.x), acc, false);
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, k.y),
-                                              __builtin_bit_cast(bf16x2_t, q.y), acc, false);
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, k.z),
-                                              __builtin_bit_cast(bf16x2_t, q.z), acc, false);
-        acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, k.w),
-                                              __builtin_bit_cast(bf16x2_t, q.w), acc, false);
-        return acc;
-    }
-    static __device__ __forceinline__ void axpy(uint4 v, float w, float *acc)
-    {
-        acc[0] += w * bf16_lo(v.x); acc[1] += w * bf16_hi(v.x);
-        acc[2] += w * bf16_lo(v.y); acc[3] += w * bf16_hi(v.y);
-        acc[4] += w * bf16_lo(v.z); acc[5] += w * bf16_hi(v.z);
-        acc[6] += w * bf16_lo(v.w); acc[7] += w * bf16_hi(v.w);
-    }
-};
-template <> struct Dot<float> {
-    static __device__ __forceinline__ float f(uint4 k, uint4 q, float acc)
-    {
-        acc = fmaf(__uint_as_float(k.x), __uint_as_float(q.x), acc);
-        acc = fmaf(__uint_as_float(k.y), __uint_as_float(q.y), acc);
-        acc = fmaf(__uint_as_float(k.z), __uint_as_float(q.z), acc);
-        acc = fmaf(__uint_as_float(k.w), __uint_as_float(q.w), acc);
-        return acc;
-    }
-    static __device__ __forceinline__ void axpy(uint4 v, float w, float *acc)
-    {
-        acc[0] += w * __uint_as_float(v.x); acc[1] += w * __uint_as_float(v.y);
-        acc[2] += w * __uint_as_float(v.z); acc[3] += w * __uint_as_float(v.w);
-    }
-};
-
-// Reduce-scatter inside a quad: lane p of the quad holds partial sums a0..a3 of
-// four dot products; on return it holds the full (4-lane) sum of dot product p.
-// Two butterfly steps: at each one a lane keeps the half of its values whose
-// index bit matches its own lane bit and sends the other half to its partner.
-__device__ __forceinline__ float quad_transpose_sum(float a0, float a1, float a2, float a3, int p)
-{
-    const bool b0 = (p & 1) != 0, b1 = (p & 2) != 0;
-    const float keep0 = b0 ? a1 : a0, send0 = b0 ? a0 : a1;
-    const float keep1 = b0 ? a3 : a2, send1 = b0 ? a2 : a3;
-    const float r0 = keep0 + dpp_f32<kQuadXor1>(send0);   // dot 0 + b0
-    const float r1 = keep1 + dpp_f32<kQuadXor1>(send1);   // dot 2 + b0
-    const float keep = b1 ? r1 : r0, send = b1 ? r0 : r1;
-    return keep + dpp_f32<kQuadXor2>(send);                // dot 2*b1 + b0
-}
-
-// Full scores of a G-head group after each lane of a quad accumulated its quarter
-// of every row: lane p returns the scores of heads p and p + 4 (when they exist).
-template <int G>
-__device__ __forceinline__ void group_scores(const float (&acc)[G], int p, float &s_lo, float &s_hi)
-{
-    if constexpr (G == 1) {
-        s_lo = quad_sum(acc[0]);
-        s_hi = 0.0f;
-    } else if constexpr (G == 2) {
-        const bool b0 = (p & 1) != 0;
-        const float r = (b0 ? acc[1] : acc[0]) + dpp_f32<kQuadXor1>(b0 ? acc[0] : acc[1]);
-        s_lo = r + dpp_f32<kQuadXor2>(r);
-        s_hi = 0.0f;
-    } else if constexpr (G == 4) {
-        s_lo = quad_transpose_sum(acc[0], acc[1], acc[2], acc[3], p);
-        s_hi = 0.0f;
-    } else {
-        s_lo = quad_transpose_sum(acc[0], acc[1], acc[2], acc[3], p);
-        s_hi = quad_transpose_sum(acc[4], acc[5], acc[6], acc[7], p);
-    }
-}
-
-// Reduce-scatter inside an octet of lanes (8 lanes per row, one per head of an
-// 8-head group): lane o holds partial sums of the 8 dot products and returns the
-// full (8-lane) sum of dot product o.  Three butterfly steps, as in
-// quad_transpose_sum; the first pairs lane o with lane 7 - o (a DPP half-row
-// mirror), whose bit 2 is the opposite of o's, which is all the step needs.
-__device__ __forceinline__ float octet_transpose_sum(const float (&acc)[8], int o)
-{
-    const bool b2 = (o & 4) != 0, b1 = (o & 2) != 0, b0 = (o & 1) != 0;
-    float h4[4], h2[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)   // heads (o & 4) + i
-        h4[i] = (b2 ? acc[i + 4] : acc[i]) + dpp_f32<kHalfMirror>(b2 ? acc[i] : acc[i + 4]);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)   // heads (o & 6) + i
-        h2[i] = (b1 ? h4[i + 2] : h4[i]) + dpp_f32<kQuadXor2>(b1 ? h4[i] : h4[i + 2]);
-    return (b0 ? h2[1] : h2[0]) + dpp_f32<kQuadXor1>(b0 ? h2[0] : h2[1]);   // head o
-}
-
-// ---------------------------------------------------------------------------
-// q_bar = fl32(q / ||q||_2), norm in float64 (Eq. 5, Eq. 6)
-// ---------------------------------------------------------------------------
-
-template <typename T, int D, int NT>
-__device__ void block_qbar(const T *q, float *s_qbar, double *red)
-{
-    static_assert(NT >= D, "one thread per element");
-    const int t = threadIdx.x;
-    double x = t < D ? elem_f64<T>(q, t) : 0.0;
-    double ss = block_reduce<NT>(x * x, red, [](double a, double b) { return a + b; });
-    double nrm = sqrt(ss);
-    if (t < D) s_qbar[t] = nrm > 0.0 ? (float)(x / nrm) : 0.0f;
-    __syncthreads();
-}
-
 
 // ---------------------------------------------------------------------------
 // k_sim: rho for 64 cache slots per block (Eq. 6)
@@ -1184,24 +855,24 @@ __global__ __launch_bounds__(kScoreThreads) void k_filter(StepArgs a, Ws w, Geom
     // for the next step
     if (a.mode == MODE_SELECT && blockIdx.x == 0)
         for (int i = tid; i < a.B * a.Hq; i += NT) w.reuse[i] = 0;
-    // the filter blocks of (virtual) head vh run on XCD vh % 8 (block j is placed
+    // the filter blocks of head bh run on XCD bh % 8 (block j is placed
     // on XCD j % 8), where the head's range blocks wrote its path and candidates
     // and its final blocks read the survivors
     const int x8 = (int)blockIdx.x & 7, rest = (int)blockIdx.x >> 3;
     const int f = rest % geo.filter_blocks_per_head;
-    const int vh = (rest / geo.filter_blocks_per_head) * 8 + x8;
-    if (vh >= a.B * a.Hq * a.U) return;
-    const int64_t len = a.U > 1 ? a.len + vh / (a.B * a.Hq) : a.len;
+    const int bh = (rest / geo.filter_blocks_per_head) * 8 + x8;
+    if (bh >= a.B * a.Hq) return;
+    const int64_t len = a.len;
     if (a.mode == MODE_SELECT) {
-        const int8_t path = w.path[vh];
+        const int8_t path = w.path[bh];
         if (path == PATH_REUSE) return;
         if (path == PATH_REUSE_SCANNED) {
             // Eq. 10 from the scan's scores: the candidate indices of range r
             // (blocks f, f + fpb, ... of the head) become their ranks
             for (int r = f; r < kCandRanges; r += geo.filter_blocks_per_head) {
-                uint64_t *ents = w.cand_ent + ((int64_t)vh * kCandRanges + r) * a.cand_cap;
-                const int n = (int)w.cand_cnt[(int64_t)vh * kCandRanges + r];
-                const float *srow = w.scores + (int64_t)vh * a.row_stride;
+                uint64_t *ents = w.cand_ent + ((int64_t)bh * kCandRanges + r) * a.cand_cap;
+                const int n = (int)w.cand_cnt[(int64_t)bh * kCandRanges + r];
+                const float *srow = w.scores + (int64_t)bh * a.row_stride;
                 for (int j0 = tid; j0 < n; j0 += 4 * NT) {
                     uint32_t idx[4];
                     float sc[4];
@@ -1221,7 +892,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_filter(StepArgs a, Ws w, Geom
     // This block's scores (or, after k_scan_list, the region's count and its
     // first 2 * NT local survivors) and the head's histogram in one round trip.
     const int64_t i0 = (int64_t)f * kFilterRows + (int64_t)tid * EPT;
-    uint64_t *reg = w.surv + (int64_t)vh * a.row_stride + (int64_t)f * kFilterRows;
+    uint64_t *reg = w.surv + (int64_t)bh * a.row_stride + (int64_t)f * kFilterRows;
     float4 v0, v1;
     uint4 lv, lv2 = {};
     uint32_t nloc = 0u;
@@ -1229,7 +900,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_filter(StepArgs a, Ws w, Geom
     // the last whole region are in the score row
     const bool listed = geo.list_mode && f < (int)(len / kFilterRows);
     if (listed) {
-        nloc = w.surv_cnt[(int64_t)vh * a.n_regions + f];
+        nloc = w.surv_cnt[(int64_t)bh * a.n_regions + f];
         if (a.K > 512) {
             lv = ((const uint4 *)reg)[2 * tid];
             lv2 = ((const uint4 *)reg)[2 * tid + 1];
@@ -1237,11 +908,11 @@ __global__ __launch_bounds__(kScoreThreads) void k_filter(StepArgs a, Ws w, Geom
             lv = ((const uint4 *)reg)[tid];
         }
     } else {
-        const float4 *src = (const float4 *)(w.scores + (int64_t)vh * a.row_stride + i0);
+        const float4 *src = (const float4 *)(w.scores + (int64_t)bh * a.row_stride + i0);
         v0 = src[0];
         v1 = src[1];
     }
-    const uint32_t *hist = w.hist + (int64_t)vh * kHistBins;
+    const uint32_t *hist = w.hist + (int64_t)bh * kHistBins;
     uint32_t c[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) c[j] = hist[kHistBins - 1 - 4 * tid - j];
@@ -1293,7 +964,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_filter(StepArgs a, Ws w, Geom
 #pragma unroll
         for (int u = 0; u < EPT; ++u)
             if ((keep >> u) & 1u) reg[pos++] = e[u];
-        if (tid == 0) w.surv_cnt[(int64_t)vh * a.n_regions + f] = total;
+        if (tid == 0) w.surv_cnt[(int64_t)bh * a.n_regions + f] = total;
         return;
     }
     const float sv[EPT] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
@@ -1306,11 +977,11 @@ __global__ __launch_bounds__(kScoreThreads) void k_filter(StepArgs a, Ws w, Geom
     }
     uint32_t total;
     uint32_t pos = block_excl_scan<NT>(n, s_red, &total);
-    uint64_t *dst = w.surv + (int64_t)vh * a.row_stride + (int64_t)f * kFilterRows;
+    uint64_t *dst = w.surv + (int64_t)bh * a.row_stride + (int64_t)f * kFilterRows;
 #pragma unroll
     for (int e = 0; e < EPT; ++e)
         if ((keep >> e) & 1u) dst[pos++] = rank_of(sv[e], (uint32_t)(i0 + e));
-    if (tid == 0) w.surv_cnt[(int64_t)vh * a.n_regions + f] = total;
+    if (tid == 0) w.surv_cnt[(int64_t)bh * a.n_regions + f] = total;
 }
 
 // ---------------------------------------------------------------------------
@@ -1508,47 +1179,6 @@ struct FastSmem {
     uint32_t wsel[kFinalThreads / 64];
     uint32_t n_tie;
 };
-
-// The bin b* that holds the k-th largest of the entries counted in hist (nb bins,
-// descending from bin nb - 1), the count above it and its own count, found by one
-// wave (every wave gets the same result): lane l sums bins nb-1-BPL*l ..
-// nb-BPL-BPL*l, a wave prefix sum finds the lane, that lane walks its bins.
-template <int NB>
-__device__ __forceinline__ void wave_find_bin(const uint32_t *hist, uint32_t k, uint32_t &bstar,
-                                              uint32_t &above, uint32_t &cnt)
-{
-    constexpr int BPL = NB / 64;
-    static_assert(BPL % 4 == 0, "whole 16-byte reads");
-    const int lane = threadIdx.x & 63;
-    uint32_t c[BPL], mine = 0u;
-    const uint4 *hv = (const uint4 *)&hist[NB - BPL * (lane + 1)];
-#pragma unroll
-    for (int i = 0; i < BPL / 4; ++i) {
-        const uint4 x = hv[i];
-        c[BPL - 1 - 4 * i] = x.x;
-        c[BPL - 2 - 4 * i] = x.y;
-        c[BPL - 3 - 4 * i] = x.z;
-        c[BPL - 4 - 4 * i] = x.w;
-    }
-#pragma unroll
-    for (int i = 0; i < BPL; ++i) mine += c[i];
-    const uint32_t inc = wave_incl_scan(mine);
-    const uint64_t hit = __ballot(inc - mine < k && inc >= k);
-    const int src = __builtin_ctzll(hit);   // k <= total: exactly one lane
-    uint32_t bs = 0u, ab = 0u, cb = 0u, run = inc - mine;
-#pragma unroll
-    for (int i = 0; i < BPL; ++i) {
-        if (run < k && run + c[i] >= k) {
-            bs = (uint32_t)(NB - 1 - BPL * lane - i);
-            ab = run;
-            cb = c[i];
-        }
-        run += c[i];
-    }
-    bstar = (uint32_t)__builtin_amdgcn_readlane((int)bs, src);
-    above = (uint32_t)__builtin_amdgcn_readlane((int)ab, src);
-    cnt = (uint32_t)__builtin_amdgcn_readlane((int)cb, src);
-}
 
 // Block (bh, slice) of k_final on the fast path, one of NS slice blocks of the
 // head, holding up to EPT entries per thread.  Returns false, with every thread
@@ -1944,16 +1574,12 @@ __device__ bool final_fast(const StepArgs &a, const Ws &w, int bh, int slice, Fa
     return true;
 }
 
-// kMulti: built for launches of several query positions (a.U > 1, the batched
-// prefill); the decode-step build keeps u = 0 out of its code.
-template <typename T, int D, bool kMulti, int NSL, int EPT>
+template <typename T, int D, int NS, int EPT>
 __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
 {
     constexpr int NT = kFinalThreads;
     constexpr int NW = NT / 64;
-    // the multi-position (prefill) build writes no output: one block per head
-    constexpr int NS = kMulti ? 1 : NSL;
-    constexpr int DS = D / NSL;                          // elements per slice
+    constexpr int DS = D / NS;                           // elements per slice
     constexpr int SB = DS * (int)sizeof(T);              // bytes per slice row
     constexpr int LPR = SB / 16;                         // lanes per slice row
     constexpr int RPW = 64 / LPR;                        // rows per wave instruction
@@ -1966,26 +1592,14 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
     __shared__ float s_part[4 * (NT / 64)][DS + 1];
     static_assert(NT * EPT <= kEntCache, "the fast path stages its entries in sm.ent");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int vh, slice;
-    if constexpr (kMulti) {
-        vh = blockIdx.x;
-        slice = 0;
-    } else {
-        // the NS blocks of head vh run on XCD vh % 8 (block j is placed on XCD
-        // j % 8), beside the range blocks that wrote the head's candidates
-        const int x = (int)blockIdx.x & 7, rest = (int)blockIdx.x >> 3;
-        slice = rest % NS;
-        vh = (rest / NS) * 8 + x;
-        if (vh >= a.B * a.Hq) return;
-    }
+    // the NS blocks of head bh run on XCD bh % 8 (block j is placed on XCD j % 8),
+    // beside the range blocks that wrote the head's candidates
+    const int x8 = (int)blockIdx.x & 7, rest = (int)blockIdx.x >> 3;
+    const int slice = rest % NS, bh = (rest / NS) * 8 + x8;
+    if (bh >= a.B * a.Hq) return;
     const bool writes_out = a.out != nullptr && a.mode != MODE_PREFILL;
     if (slice != 0 && !writes_out) return;
-    // Virtual head vh = u * B * Hq + bh: query position u of head bh (u = 0 unless
-    // a batched prefill launch); the workspaces are indexed by vh, the cache, q
-    // and the outputs by bh.
-    const int u = kMulti ? vh / (a.B * a.Hq) : 0;
-    const int bh = kMulti ? vh - u * a.B * a.Hq : vh;
-    const int64_t len = kMulti ? a.len + u : a.len;
+    const int64_t len = a.len;
 
     if (slice == 0 && (a.mode == MODE_REFRESH || a.mode == MODE_COLD)) {
         const int8_t code = a.mode == MODE_REFRESH ? PATH_REFRESH : PATH_COLD;
@@ -1996,11 +1610,8 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
         if (a.dbg_ret)
             for (int i = tid; i < a.R; i += NT) a.dbg_ret[(int64_t)bh * a.R + i] = -1;
     }
-    if constexpr (!kMulti) {
-        if (writes_out && final_fast<T, D, NS, EPT>(a, w, bh, slice, fs, sm.ent, sm.sel, s_part))
-            return;
-        __syncthreads();   // the general path follows the fast path's early exit
-    }
+    if (writes_out && final_fast<T, D, NS, EPT>(a, w, bh, slice, fs, sm.ent, sm.sel, s_part)) return;
+    __syncthreads();   // the general path follows the fast path's early exit
 
     // Path, the region counts of both layouts and the first entries of every
     // region in one round trip (the entry loads are speculative: a region's
@@ -2015,7 +1626,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
     for (int u = 0; u < kRegPerThread; ++u) {
         const int r = tid * rpt + u;
         const bool ok = u < rpt && r < nreg_s;
-        const uint32_t x = w.surv_cnt[(int64_t)vh * a.n_regions + (ok ? r : 0)];
+        const uint32_t x = w.surv_cnt[(int64_t)bh * a.n_regions + (ok ? r : 0)];
         scnt[u] = ok ? x : 0u;
     }
     const uint32_t ccnt_l = w.cand_cnt[(int64_t)bh * kCandRanges + (tid < kCandRanges ? tid : 0)];
@@ -2027,7 +1638,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
         rg.stride = a.cand_cap;
         rg.nreg = kCandRanges;
     } else {
-        rg.base = w.surv + (int64_t)vh * a.row_stride;
+        rg.base = w.surv + (int64_t)bh * a.row_stride;
         rg.stride = kFilterRows;
         rg.nreg = nreg_s;
     }
@@ -2266,7 +1877,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
     }
     if (a.do_insert) {
         // Sec. 3.4: insert (q_bar, support) after either path.
-        const int64_t e = (int64_t)bh * a.M + (kMulti ? (a.insert_slot + u) % a.M : a.insert_slot);
+        const int64_t e = (int64_t)bh * a.M + a.insert_slot;
         if (owns(1)) {
             for (int t = tid; t < a.K; t += NT)
                 w.supp[e * a.K + t] = t < kn ? (int32_t)(sm.sel[t] >> 32) : -1;
@@ -2276,8 +1887,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
             if (a.mode == MODE_SELECT) {
                 for (int t = tid; t < D; t += NT) w.qbar[e * D + t] = w.qbar_cur[(int64_t)bh * D + t];
             } else {
-                const T *q = (const T *)a.q + (int64_t)bh * a.q_head_stride + (int64_t)u * D;
-                block_qbar<T, D, NT>(q, sm.qbar, sm.red64);
+                block_qbar<T, D, NT>((const T *)a.q + (int64_t)bh * a.q_head_stride, sm.qbar, sm.red64);
                 for (int t = tid; t < D; t += NT) w.qbar[e * D + t] = sm.qbar[t];
             }
         }
@@ -2290,145 +1900,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
             }
         } else {
             // leave the histogram zeroed for the next launch
-            for (int i = tid; i < kHistBins; i += NT) w.hist[(int64_t)vh * kHistBins + i] = 0u;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Batched prefill initialisation (Sec. 3.3): the prompt-tail queries of U
-// positions at once, each against its causal prefix
-// ---------------------------------------------------------------------------
-
-
-// k_pf_score: the scores of Eq. 4 for U positions x G heads of a KV group (the
-// group's "virtual queries", vq = u * G + j) as a matrix product on the matrix
-// cores.  Block (pair, tile) takes keys [kc * kPfKeys, ...) of KV group grp for
-// the kPfCols virtual queries of query tile `tile`, in column tiles of 16, with
-// v_mfma_f32_16x16x32_bf16: the A operand is 16 key rows x 32 dims, B is 32 dims
-// x 16 queries, and lane l supplies key row (and query) l % 16 for dims
-// 8 (l / 16) .. + 7 of each 32-dim step and receives keys 4 (l / 16) .. + 3 of
-// query l % 16.  Each key tile loaded serves every column tile.  Keys at or past
-// a query's causal length are left out of its histogram (LDS, two 16-bit counts
-// per word, added to the global histogram at the end); every score is stored to
-// the virtual head's score row, those past the causal length included (no later
-// stage reads them), so that each wave issues the same stores every iteration
-// and its key loads, two iterations ahead, never wait for them.  The blocks of
-// one (group, key chunk) pair share blockIdx % 8, so they run on one XCD and
-// read the chunk's keys through one L2.
-template <int D>
-__global__ __launch_bounds__(kPfThreads) void k_pf_score(StepArgs a, Ws w, Geometry geo)
-{
-    constexpr int NT = kPfThreads, NW = NT / 64, TW = kPfTiles, KS = D / 32;
-    constexpr int CT = kPfCols / 16;
-    constexpr int ROWS = NW * TW * 16;
-    constexpr int ITERS = kPfKeys / ROWS;
-    // A chunk's stores stay inside its score row: chunks end on filter-region
-    // boundaries, and score rows are whole regions long.
-    static_assert(D % 32 == 0 && kPfKeys % (2 * ROWS) == 0 && kFilterRows % kPfKeys == 0 &&
-                  kPfCols % 16 == 0, "tile geometry");
-    static_assert(kPfKeys < 65536 && kPfHistStride * 2 > kHistBins, "16-bit bin counts");
-    __shared__ uint32_t s_hist[kPfCols * kPfHistStride];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 15, kq = lane >> 4;
-    const int j = (int)blockIdx.x;
-    const int pair = (j & 7) + 8 * (j / (8 * geo.pf_qtiles));
-    const int tile = (j >> 3) % geo.pf_qtiles;
-    if (pair >= geo.pf_pairs) return;
-    const int grp = pair / geo.pf_kchunks, kc = pair % geo.pf_kchunks;
-    const int b = grp / a.Hkv, g = grp % a.Hkv;
-    const int BH = a.B * a.Hq;
-    const int nvq = a.G * a.U;
-    // rows of this block: the chunk, cut at the longest causal length of the tile
-    const int last_vq = (tile + 1) * kPfCols - 1 < nvq - 1 ? (tile + 1) * kPfCols - 1 : nvq - 1;
-    const int64_t tlen = a.len + last_vq / a.G;
-    const int64_t k0 = (int64_t)kc * kPfKeys;
-    const int64_t k1 = k0 + kPfKeys < tlen ? k0 + kPfKeys : tlen;
-    if (k0 >= k1) return;
-
-    // This lane's virtual query in each column tile; columns past the last one
-    // repeat it (same query, same score row, same values stored) and count nothing.
-    bf16x8_t qb[CT][KS];
-    float *srow[CT];
-    int64_t cend[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-        const int vq = tile * kPfCols + ct * 16 + col;
-        const bool cvalid = vq < nvq;
-        const int vqe = cvalid ? vq : nvq - 1;
-        const int u = vqe / a.G;
-        const int bh = b * a.Hq + g * a.G + vqe % a.G;
-        const uint4 *qr = (const uint4 *)((const uint16_t *)a.q + (int64_t)bh * a.q_head_stride +
-                                          (int64_t)u * D);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qb[ct][ks] = __builtin_bit_cast(bf16x8_t, qr[ks * 4 + kq]);
-        srow[ct] = w.scores + ((int64_t)u * BH + bh) * a.row_stride;
-        const int64_t clen = cvalid ? a.len + u : 0;
-        cend[ct] = clen < k1 ? clen : k1;           // rows counted for this query
-    }
-    const uint16_t *kbase = (const uint16_t *)a.k + ((int64_t)b * a.Hkv + g) * a.max_len * D;
-    auto load = [&](uint4 (&kv)[TW][KS], int64_t base) {
-#pragma unroll
-        for (int t = 0; t < TW; ++t) {
-            const int64_t r = base + (wave * TW + t) * 16 + col;
-            const uint4 *rp = (const uint4 *)(kbase + (r < k1 ? r : k0) * D);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) kv[t][ks] = rp[ks * 4 + kq];
-        }
-    };
-    // One iteration: the scores of ROWS keys from kv, the loads of the keys two
-    // iterations on into kv, the stores and the histogram counts.
-    auto step = [&](uint4 (&kv)[TW][KS], int64_t base) {
-        f32x4_t acc[CT][TW];
-#pragma unroll
-        for (int t = 0; t < TW; ++t)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                acc[ct][t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    acc[ct][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8_t, kv[t][ks]), qb[ct][ks], acc[ct][t], 0, 0, 0);
-            }
-        load(kv, base + 2 * ROWS);   // past k1 the clamped rows are re-read, never used
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            uint32_t *hrow = s_hist + (ct * 16 + col) * kPfHistStride;
-#pragma unroll
-            for (int t = 0; t < TW; ++t) {
-                const int64_t r4 = base + (wave * TW + t) * 16 + 4 * kq;
-                const float sc[4] = {acc[ct][t][0] * a.inv_sqrt_d, acc[ct][t][1] * a.inv_sqrt_d,
-                                     acc[ct][t][2] * a.inv_sqrt_d, acc[ct][t][3] * a.inv_sqrt_d};
-                *(float4 *)(srow[ct] + r4) = make_float4(sc[0], sc[1], sc[2], sc[3]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (r4 + i < cend[ct]) {
-                        const uint32_t bin = ord_key(sc[i]) >> kHistShift;
-                        atomicAdd(&hrow[bin >> 1], 1u << ((bin & 1u) << 4));
-                    }
-                }
-            }
-        }
-    };
-    uint4 kva[TW][KS], kvb[TW][KS];
-    load(kva, k0);   // the first key rows are in flight while the histogram is cleared
-    load(kvb, k0 + ROWS);
-    for (int i = tid; i < kPfCols * kPfHistStride; i += NT) s_hist[i] = 0u;
-    __syncthreads();
-    // A fixed trip count: rows past k1 (the chunk cut short by the causal limit)
-    // are computed from clamped loads and stored where nothing reads them.
-    for (int it = 0; it < ITERS; it += 2) {
-        step(kva, k0 + (int64_t)it * ROWS);
-        step(kvb, k0 + (int64_t)(it + 1) * ROWS);
-    }
-    __syncthreads();
-    for (int i = tid; i < kPfCols * kHistBins; i += NT) {
-        const int c = i / kHistBins, bin = i % kHistBins;
-        const int cvq = tile * kPfCols + c;
-        const uint32_t n = (s_hist[c * kPfHistStride + (bin >> 1)] >> ((bin & 1) << 4)) & 0xFFFFu;
-        if (n && cvq < nvq) {
-            const int cbh = b * a.Hq + g * a.G + cvq % a.G;
-            atomicAdd(&w.hist[((int64_t)(cvq / a.G) * BH + cbh) * kHistBins + bin], n);
+            for (int i = tid; i < kHistBins; i += NT) w.hist[(int64_t)bh * kHistBins + i] = 0u;
         }
     }
 }
@@ -3005,16 +2477,11 @@ int final_ept(const StepArgs &a) { return (int64_t)a.R * a.K + a.W > 4608 ? 16 :
 template <typename T, int D>
 static void final_desc(const StepArgs &a, KernelDesc *k)
 {
-    if (a.U > 1) {
-        *k = KernelDesc{(const void *)&k_final<T, D, true, 8, 8>, dim3((unsigned)(a.B * a.Hq * a.U)),
-                        dim3(kFinalThreads), 0u, 2};
-        return;
-    }
     const int ns = final_slices(a), ept = final_ept(a);
     const void *f;
-    if (ns == 8) f = ept == 8 ? (const void *)&k_final<T, D, false, 8, 8> : (const void *)&k_final<T, D, false, 8, 16>;
-    else if (ns == 4) f = ept == 8 ? (const void *)&k_final<T, D, false, 4, 8> : (const void *)&k_final<T, D, false, 4, 16>;
-    else f = ept == 8 ? (const void *)&k_final<T, D, false, 2, 8> : (const void *)&k_final<T, D, false, 2, 16>;
+    if (ns == 8) f = ept == 8 ? (const void *)&k_final<T, D, 8, 8> : (const void *)&k_final<T, D, 8, 16>;
+    else if (ns == 4) f = ept == 8 ? (const void *)&k_final<T, D, 4, 8> : (const void *)&k_final<T, D, 4, 16>;
+    else f = ept == 8 ? (const void *)&k_final<T, D, 2, 8> : (const void *)&k_final<T, D, 2, 16>;
     // whole groups of 8 heads (one per XCD), ns blocks each
     *k = KernelDesc{f, dim3((unsigned)((a.B * a.Hq + 7) / 8 * 8 * ns)), dim3(kFinalThreads), 0u, 2};
 }
@@ -3057,15 +2524,10 @@ void describe_kernel(int which, int dtype, const StepArgs &a, const Geometry &ge
         if (bf) return d64 ? score_g<uint16_t, 64>(a, geo, k) : score_g<uint16_t, 128>(a, geo, k);
         return d64 ? score_g<float, 64>(a, geo, k) : score_g<float, 128>(a, geo, k);
     case KERNEL_FILTER:
-        // whole groups of 8 (virtual) heads, one per XCD
+        // whole groups of 8 heads, one per XCD
         *k = KernelDesc{(const void *)&k_filter,
-                        dim3((unsigned)((a.B * a.Hq * a.U + 7) / 8 * 8 * geo.filter_blocks_per_head)),
+                        dim3((unsigned)((a.B * a.Hq + 7) / 8 * 8 * geo.filter_blocks_per_head)),
                         dim3(kScoreThreads), 0u, 3};
-        return;
-    case KERNEL_PF_SCORE:   // bf16 only
-        *k = KernelDesc{d64 ? (const void *)&k_pf_score<64> : (const void *)&k_pf_score<128>,
-                        dim3((unsigned)(((geo.pf_pairs + 7) / 8) * 8 * geo.pf_qtiles)),
-                        dim3(kPfThreads), 0u, 3};
         return;
     case KERNEL_DENSE:
         if (bf) return d64 ? dense_g<uint16_t, 64>(a, k) : dense_g<uint16_t, 128>(a, k);

@@ -164,3 +164,48 @@ def test_prefill_batched_equal_keys():
     gst = _gpu_prefill(p, w.dtype, inp.q_tail_raw, k_raw, inp.v_raw, w.prompt_len)
     assert np.array_equal(gst["supp"], ost["supp"])
     assert np.array_equal(gst["cnt"], ost["cnt"])
+
+
+BOUND_SHAPES = [
+    # label, workload changes, what the key rows are replaced with
+    # launches on both sides of the list capacity (4096): score rows, then lists
+    ("around_capacity", dict(n_q_heads=8, n_kv_heads=2, prompt_len=4103, k=64, cache_cap=20,
+                             n_centers=16), None),
+    # K = 1 and K = 2048 (list capacity 16384, group maxima of single tiles)
+    ("k1", dict(n_q_heads=4, n_kv_heads=1, prompt_len=7001, k=1, cache_cap=9, n_centers=16), None),
+    ("k2048_d64", dict(n_q_heads=2, n_kv_heads=2, head_dim=64, prompt_len=17001, k=2048,
+                       cache_cap=6, n_centers=16), None),
+    # 140 virtual queries a group: two waves side by side, padded columns; a prefix past
+    # one bitmap pass is covered by the 128K cases' last position
+    ("two_query_tiles", dict(n_q_heads=7, n_kv_heads=1, prompt_len=6003, k=40, cache_cap=20,
+                             n_centers=16), None),
+    # for about half of the queries the best keys are one run of equal rows longer than
+    # a list: those lists overflow and the positions run again with score rows
+    ("overflow", dict(n_q_heads=4, n_kv_heads=2, prompt_len=9000, k=50, cache_cap=5,
+                      n_centers=8), (1000, 7000)),
+]
+
+
+@pytest.mark.parametrize("label,change,equal", BOUND_SHAPES, ids=[s[0] for s in BOUND_SHAPES])
+def test_prefill_batched_bounds_and_lists(label, change, equal):
+    """The bounded selection of the batched prefill where it can go wrong: list
+    capacity, the smallest and largest K, padded query columns, lists that
+    overflow.  Supports exact up to near-ties, as in the other cases."""
+    w = WORKLOADS["16k"].with_(**change)
+    print(f"batched prefill {label}", flush=True)
+    inp = make_inputs(w)
+    k_raw = inp.k_raw
+    if equal is not None:
+        k_raw = k_raw.copy()
+        # equal rows, eight times as long as the others (bf16 exponent + 3): far above or
+        # far below every other score of a query
+        k_raw[:, :, equal[0]:equal[1]] = k_raw[:, :, equal[0]:equal[0] + 1] + (3 << 7)
+    kf = (k_raw.astype(np.uint32) << 16).view(np.float32)
+    p = params_of(w)
+    orc = O.Oracle(p)
+    orc.prefill_init(inp.q_tail, kf, inp.v, w.prompt_len)
+    gst = _gpu_prefill(p, w.dtype, inp.q_tail_raw, k_raw, inp.v_raw, w.prompt_len)
+    tally = Tally()
+    _compare_states(p, gst, orc.get_state(), list(range(p.heads)), inp.q_tail, kf, w.prompt_len,
+                    tally)
+    print(tally, flush=True)
