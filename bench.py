@@ -969,6 +969,7 @@ SYMBOLS = {  # kernel symbol prefix -> name used by the library's own profiling
     "retopk::k_filter(": "retopk_filter",
     "void retopk::k_final<": "retopk_final",
     "void retopk::k_dense<": "dense_chunk",
+    "void retopk::k_dense_wave<": "dense_chunk",
     "void retopk::k_dense_merge<": "dense_merge",
     "void retopk::k_pf_scan<": "prefill_score",
     "void retopk::k_pf_bound<": "retopk_filter",

@@ -86,6 +86,40 @@ retopk_status validate_config(const retopk_config *c)
     return RETOPK_OK;
 }
 
+// Rows of a full_attention chunk (one block) at length len.
+// bf16: whole 32-row tiles for 240 blocks, at least a tile for each of a block's 8
+// waves.  A CU holds one block (by its registers), so 256 CUs take 240 in one go and a
+// few blocks more start a second one (128K, 8 groups: 95.9 us at 240 and 256, 109 at
+// 260, 118 at 320, 99 at 480; 16K, 4 groups: 15.8 at 224-256, 19.9 above).  240 and not
+// 256 because chunks that start a multiple of 1 MiB apart, give or take 8 KiB, collide
+// on memory channels (1M rows of one group of 8: 101 us, 116 in chunks of 4128 rows;
+// 98 and 112 at 4064), and such sizes are stepped over.  32-bit offsets inside a chunk
+// bound it from above.  f32: the fewest rows with at most four blocks per CU.
+constexpr int kDenseRowsMin = 256, kDenseRowsMax = 65536, kDenseBlocks = 240;
+int dense_rows(const retopk_config &c, int64_t len)
+{
+    const int64_t groups = (int64_t)c.batch * c.n_kv_heads;
+    if (c.dtype == RETOPK_BF16) {
+        int64_t r = ceil_div(ceil_div(groups * len, kDenseBlocks), 32) * 32;
+        const int64_t off = r * c.head_dim * 2 % (1 << 20);
+        if (r > kDenseRowsMin && (off < 16384 || off > (1 << 20) - 16384)) r += 128;
+        return (int)(r < kDenseRowsMin ? kDenseRowsMin : r > kDenseRowsMax ? kDenseRowsMax : r);
+    }
+    int r = kDenseRowsMin;
+    while (r < kDenseRows && groups * ceil_div(len, r) > 4 * kCUs) r *= 2;
+    return r;
+}
+
+// The most chunks dense_rows gives any length up to max_len.
+int dense_chunks(const retopk_config &c)
+{
+    const int64_t groups = (int64_t)c.batch * c.n_kv_heads;
+    const bool bf = c.dtype == RETOPK_BF16;
+    const int64_t spread = ceil_div((bf ? 1 : 4) * kCUs, groups);
+    const int64_t most = ceil_div(c.max_len, bf ? kDenseRowsMax : kDenseRows);
+    return (int)(spread > most ? spread : most);
+}
+
 StepArgs config_args(const retopk_config &c)
 {
     StepArgs a{};
@@ -101,7 +135,7 @@ StepArgs config_args(const retopk_config &c)
     a.W = c.window;
     a.cand_cap = c.r * c.k + c.window;
     a.n_regions = (int)ceil_div(c.max_len, kFilterRows);
-    a.n_dense = (int)ceil_div(c.max_len, kDenseRows);
+    a.n_dense = dense_chunks(c);
     a.row_stride = (int64_t)a.n_regions * kFilterRows;
     a.tau = c.tau;
     a.retrieval = c.retrieval;
@@ -527,8 +561,7 @@ retopk_status retopk_create(const retopk_config *cfg, retopk_handle *out)
         (st = alloc(h, &w.cand_ent, (size_t)(BH * kCandRanges * h->cand_cap))) != RETOPK_OK ||
         (st = alloc(h, &w.cand_cnt, (size_t)(BH * kCandRanges))) != RETOPK_OK ||
         (st = alloc(h, &w.stats, (size_t)STAT_COUNT)) != RETOPK_OK ||
-        (st = alloc(h, &w.dense_part, (size_t)(BH * ceil_div(cfg->max_len, kDenseRows) *
-                                                (cfg->head_dim + 2)))) != RETOPK_OK) {
+        (st = alloc(h, &w.dense_part, (size_t)(BH * dense_chunks(*cfg) * (cfg->head_dim + 2)))) != RETOPK_OK) {
         retopk_destroy(h);
         return st;
     }
@@ -702,6 +735,7 @@ retopk_status full_attention(retopk_handle h, const void *q, const void *k, cons
     hipStream_t s = (hipStream_t)stream;
     if (hipSetDevice(h->device) != hipSuccess) return fail(h);
     if (order_after_last(h, s) != RETOPK_OK) return RETOPK_ERR_HIP;
+    a.dense_rows = dense_rows(h->cfg, len);
     const Geometry geo = make_geometry(h, len, MODE_EXACT);
     Ws wv = h->w;
     void *args[3] = {&a, &wv, nullptr};

@@ -11,6 +11,9 @@ namespace retopk {
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// 16 bytes as one register value (HIP's uint4 is a struct, whose arrays the compiler
+// keeps in scratch memory where they live across a loop with a barrier in it).
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Scalar helpers
@@ -149,6 +152,38 @@ __device__ __forceinline__ float row_ror_f32(float x, int n)
     default: r = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128, 0xF, 0xF, true); break;
     }
     return __builtin_bit_cast(float, r);
+}
+
+// gfx950 row swaps: permlane32_swap exchanges the first operand's upper 32 lanes with
+// the second's lower 32, permlane16_swap the first's odd rows of 16 lanes with the
+// second's even ones.  add32_f32(x, y): lanes 0-31 get the sum of x over lanes i and
+// i ^ 32, lanes 32-63 that of y (add16_f32: even rows x, odd rows y, over i and i ^ 16);
+// with x == y every lane gets the full sum.
+__device__ __forceinline__ float add32_f32(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add16_f32(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// The largest of x over lanes i, i ^ 16, i ^ 32 and i ^ 48.
+__device__ __forceinline__ float max_rows_f32(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+
+// Orders LDS accesses of the lanes of one wave (LDS runs them in program order; this
+// keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)

@@ -92,7 +92,8 @@ struct StepArgs {
     int K, M, R, W;
     int cand_cap;
     int n_regions;             // ceil(max_len / kFilterRows): surv_cnt row length
-    int n_dense;               // ceil(max_len / kDenseRows): dense_part chunks per head
+    int n_dense;               // dense_part chunks per head (most for any length)
+    int dense_rows;            // rows of a full_attention chunk
     int64_t row_stride;        // n_regions * kFilterRows: row length of scores and surv
     float tau;
     int retrieval;             // 0: R most similar entries (Eq. 7); 1: R most recent
@@ -180,9 +181,10 @@ struct KernelDesc {
 enum : int { KERNEL_SIM = 0, KERNEL_SCORE = 1, KERNEL_FILTER = 2, KERNEL_FINAL = 3,
               KERNEL_DENSE = 4, KERNEL_DENSE_MERGE = 5 };
 
-// Full (dense) attention: rows per chunk block, and the chunk count for a length.
+// Full (dense) attention: most rows of a chunk block.
 constexpr int kDenseRows = 1024;
-constexpr int kDenseThreads = 512;
+constexpr int kDenseWaveThreads = 512;   // bf16 blocks
+constexpr int kDenseThreads = 512;       // f32 blocks
 constexpr int kMergeThreads = 1024;  // dense merge block: one per query head
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -195,6 +197,7 @@ inline int64_t heads_of(const retopk_config &c) { return (int64_t)c.batch * c.n_
 retopk_status validate_config(const retopk_config *c);
 StepArgs config_args(const retopk_config &c);
 void range_split(StepArgs &a);
+int dense_rows(const retopk_config &c, int64_t len);
 Geometry step_geometry(const retopk_config &c, int64_t len, int mode);
 
 // Fills *k for kernel `which` of a step in a.mode (retopk_kernels.hip).

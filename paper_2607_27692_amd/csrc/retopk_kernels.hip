@@ -37,6 +37,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 namespace retopk {
 
 // ---------------------------------------------------------------------------
@@ -1909,7 +1911,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
 // Full attention (the dense baseline): softmax over every row, then V
 // ---------------------------------------------------------------------------
 
-// k_dense: block (b, g, c) takes rows [c * kDenseRows, ...) of KV group (b, g) for
+// k_dense (f32): block (b, g, c) takes rows [c * dense_rows, ...) of KV group (b, g) for
 // the G query heads of the group (one key or value row load serves all of them):
 // scores with the scan's row geometry, then per head the chunk's maximum m, the
 // weights exp(s - m), their sum l and the weighted sum o of the value rows.
@@ -1928,12 +1930,12 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
     __shared__ float s_ml[2][G];            // each head's chunk maximum and weight sum
     __shared__ float s_o[NW][G][D];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, p = lane & 3, rl = lane >> 2;
-    const int nch = (int)((a.len + kDenseRows - 1) / kDenseRows);
+    const int nch = (int)((a.len + a.dense_rows - 1) / a.dense_rows);
     const int c = blockIdx.x % nch, bg = blockIdx.x / nch;
     const int b = bg / a.Hkv, g = bg % a.Hkv;
     const int bh0 = b * a.Hq + g * a.G;      // heads past a.G pad the group
-    const int64_t r0 = (int64_t)c * kDenseRows;
-    const int nrow = (int)(a.len - r0 < kDenseRows ? a.len - r0 : kDenseRows);
+    const int64_t r0 = (int64_t)c * a.dense_rows;
+    const int nrow = (int)(a.len - r0 < a.dense_rows ? a.len - r0 : a.dense_rows);
     const T *kbase = (const T *)a.k + ((int64_t)b * a.Hkv + g) * a.max_len * D;
     const T *vbase = (const T *)a.v + ((int64_t)b * a.Hkv + g) * a.max_len * D;
 
@@ -2017,6 +2019,20 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
         }
     }
     }
+    // The first value rows are in flight during the softmax: VL lanes per value row,
+    // each holding EPV elements for every head; rows spread over the waves (VU rows
+    // per lane in flight, clamped to in-bounds rows).
+    constexpr int VU = G == 8 ? 2 : 4;
+    const int sub = lane / VL, vl = lane % VL;
+    uint4 raw[VU];
+    auto load_v = [&](int t0) {
+#pragma unroll
+        for (int u = 0; u < VU; ++u) {
+            const int t = t0 + u * NW * VR + sub;
+            raw[u] = ((const uint4 *)(vbase + (r0 + (t < nrow ? t : 0)) * D))[vl];
+        }
+    };
+    load_v(wave * VR);
     __syncthreads();
     // per head: chunk maximum, then weights exp(s - m) in place and their sum
     float m[G], l[G];
@@ -2062,22 +2078,13 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
             s_ml[1][j] = l[j];
         }
     }
-    // Eq. 12 over the chunk: VL lanes per value row, each holding EPV elements
-    // for every head; rows spread over the waves (VU rows per lane in flight).
-    constexpr int VU = G == 8 ? 2 : 4;
-    const int sub = lane / VL, vl = lane % VL;
+    // Eq. 12 over the chunk
     float acc[G][EPV];
 #pragma unroll
     for (int j = 0; j < G; ++j)
 #pragma unroll
         for (int e = 0; e < EPV; ++e) acc[j][e] = 0.0f;
     for (int t0 = wave * VR; t0 < nrow; t0 += NW * VR * VU) {
-        uint4 raw[VU];
-#pragma unroll
-        for (int u = 0; u < VU; ++u) {
-            const int t = t0 + u * NW * VR + sub;
-            raw[u] = ((const uint4 *)(vbase + (r0 + (t < nrow ? t : 0)) * D))[vl];
-        }
 #pragma unroll
         for (int u = 0; u < VU; ++u) {
             const int t = t0 + u * NW * VR + sub;
@@ -2086,6 +2093,7 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
                 for (int j = 0; j < G; ++j) Dot<T>::axpy(raw[u], s_sc[j][t], acc[j]);
             }
         }
+        if (t0 + NW * VR * VU < nrow) load_v(t0 + NW * VR * VU);
     }
 #pragma unroll
     for (int o = VL; o < 64; o <<= 1)
@@ -2113,6 +2121,225 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
     }
 }
 
+// k_dense_wave: the bf16 build.  Block (b, g, c) takes rows [c * dense_rows, ...) of KV
+// group (b, g); each of its 8 waves streams its own 32-row tiles (tile w, w + 8, ...)
+// with no barrier, holding one tile's key and value rows in flight while it works on
+// the previous ones: scores on the matrix cores (v_mfma_f32_16x16x32_bf16, 16 keys x
+// 32 dims x 16 query columns, of which the first a.G are the group's heads and the
+// others repeat head 0; lane l holds the scores of keys 4 (l / 16) .. + 3 of column
+// l % 16), a running maximum per head, weights in float32 through a wave-private LDS
+// tile, and the weighted value sums in float32, VL lanes a value row for all heads.
+// The waves' (o, m, l) are combined once, at the end.  The four 32-dim products of a
+// score are summed as a tree and no value sum is a chain of more than 16 terms: against
+// float64 the outputs are 2.2e-7 off at 128K (2.3e-7 for chunks of 1024 rows).  Bound by HBM where a block has
+// many tiles (128K rows, 8 groups of 4: 93 us for 537 MB = 5.8 TB/s, the streaming
+// read's rate; the chunk-at-a-time kernel of k_dense took 100 us), by latency where it
+// has one (16K rows, 4 groups of 7: 10 us, 30 before in 64 chunks of 1024 rows).
+template <int D, int G>
+__global__ __launch_bounds__(kDenseWaveThreads, 2) void k_dense_wave(StepArgs a, Ws w)
+{
+    constexpr int NT = kDenseWaveThreads, NW = NT / 64, KS = D / 32;
+    constexpr int VL = D / 8;                        // lanes per value row (16 bytes each)
+    constexpr int VR = 64 / VL, RL = 32 / VR;        // value rows per instruction; per lane and tile
+    constexpr int FL = 16 / RL;                      // tiles between flushes: 16 terms a sum
+    __shared__ __attribute__((aligned(16))) float s_p[NW][32][G];   // a tile's weights
+    __shared__ float s_f[NW][G];                     // a tile's rescaling factors
+    __shared__ float s_m[NW][G], s_l[NW][G];
+    __shared__ float s_o[NW][G][D];
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nch = (int)((a.len + a.dense_rows - 1) / a.dense_rows);
+    const int c = blockIdx.x % nch, bg = blockIdx.x / nch;
+    const int b = bg / a.Hkv, g = bg % a.Hkv;
+    const int bh0 = b * a.Hq + g * a.G;      // heads past a.G pad the group
+    const int64_t r0 = (int64_t)c * a.dense_rows;
+    const int nrow = (int)(a.len - r0 < a.dense_rows ? a.len - r0 : a.dense_rows);
+    const uint16_t *kbase = (const uint16_t *)a.k + (((int64_t)b * a.Hkv + g) * a.max_len + r0) * D;
+    const uint16_t *vbase = (const uint16_t *)a.v + (((int64_t)b * a.Hkv + g) * a.max_len + r0) * D;
+    const int nt = (nrow + 31) / 32, n_it = wave < nt ? (nt - wave + NW - 1) / NW : 0;
+    const int sub = lane / VL, vl = lane % VL;
+
+    u32x4_t kv[2][KS], vv[RL];
+    auto load_k = [&](int it) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int r = (it * NW + wave) * 32 + t * 16 + col;
+            const u32x4_t *rp = (const u32x4_t *)(kbase + (uint32_t)(r < nrow ? r : nrow - 1) * D);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) kv[t][ks] = rp[ks * 4 + kq];
+        }
+    };
+    auto load_v = [&](int it) {
+#pragma unroll
+        for (int u = 0; u < RL; ++u) {
+            const int r = (it * NW + wave) * 32 + sub * RL + u;
+            vv[u] = ((const u32x4_t *)(vbase + (uint32_t)(r < nrow ? r : nrow - 1) * D))[vl];
+        }
+    };
+    bf16x8_t qb[KS];
+    {
+        const u32x4_t *qr = (const u32x4_t *)((const uint16_t *)a.q +
+                                              (int64_t)(bh0 + (col < a.G ? col : 0)) * a.q_head_stride);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qb[ks] = __builtin_bit_cast(bf16x8_t, qr[ks * 4 + kq]);
+    }
+    float acc[G][8], m = -INFINITY, l = 0.0f;
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[j][e] = 0.0f;
+
+    auto tile = [&](int it, auto more) {
+        f32x4_t sc[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f32x4_t part[KS];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                part[ks] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kv[t][ks]), qb[ks],
+                                                                   f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+#pragma unroll
+            for (int n = KS / 2; n > 0; n /= 2)
+#pragma unroll
+                for (int ks = 0; ks < n; ++ks) part[ks] += part[ks + n];
+            sc[t] = part[0];
+        }
+        __builtin_amdgcn_sched_barrier(0);   // the next rows into the registers just read
+        if constexpr (decltype(more)::value) load_k(it + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const int row = (it * NW + wave) * 32 + 4 * kq;
+        float tm = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sc[t][i] = row + t * 16 + i < nrow ? sc[t][i] * a.inv_sqrt_d : -INFINITY;
+                tm = fmaxf(tm, sc[t][i]);
+            }
+        tm = max_rows_f32(tm);
+        const float mn = fmaxf(m, tm);               // finite: the tile has a row
+        const float f = expf(m - mn);
+        m = mn;
+        l *= f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sc[t][i] = expf(sc[t][i] - mn);
+            if (col < G)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s_p[wave][t * 16 + 4 * kq + i][col] = sc[t][i];
+        }
+        l += ((sc[0][0] + sc[0][1]) + (sc[0][2] + sc[0][3])) + ((sc[1][0] + sc[1][1]) + (sc[1][2] + sc[1][3]));
+        const bool moved = __ballot(f != 1.0f) != 0ull;
+        if (moved && lane < G) s_f[wave][lane] = f;
+        wave_lds_fence();
+        if (moved) {
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const float x = s_f[wave][j];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[j][e] *= x;
+            }
+        }
+        // Eq. 12 on the tile: this lane's RL rows, each widened once for all heads
+#pragma unroll
+        for (int u = 0; u < RL; ++u) {
+            const float *p = s_p[wave][sub * RL + u];
+            const u32x4_t x = vv[u];
+            const float v[8] = {bf16_lo(x[0]), bf16_hi(x[0]), bf16_lo(x[1]), bf16_hi(x[1]),
+                                bf16_lo(x[2]), bf16_hi(x[2]), bf16_lo(x[3]), bf16_hi(x[3])};
+            float pj[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j) pj[j] = p[j];
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[j][e] += pj[j] * v[e];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_lds_fence();
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(more)::value) load_v(it + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // Adds the running sums, reduced over the lanes that share a slice of the value row,
+    // to the wave's sums in LDS (rescaled to the current maximum) and clears them: every
+    // FL tiles, so that no sum is one long chain of terms.  Each lane swap sums two
+    // elements, so that a lane ends with 2 of its 8, elements e0, e0 + 1.
+    const int e0 = 4 * (lane >> 5) + 2 * ((lane >> 4) & 1);
+    float m_sum = -INFINITY, l_sum = 0.0f;           // the maximum they refer to; the weights' sum
+    auto flush = [&](bool first) {
+        const float fs = first ? 0.0f : expf(m_sum - m);
+        if (lane < G) s_f[wave][lane] = fs;
+        l_sum = fmaf(l_sum, fs, l);                  // by the very factor of the value sums
+        l = 0.0f;
+        m_sum = m;
+        wave_lds_fence();
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            float h[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = add32_f32(acc[j][e], acc[j][e + 4]);
+            float x = add16_f32(h[0], h[2]), y = add16_f32(h[1], h[3]);
+            if constexpr (VL == 8) {
+                x += row_ror_f32(x, 8);
+                y += row_ror_f32(y, 8);
+            }
+            float2 *o = (float2 *)&s_o[wave][j][(lane & (VL - 1)) * 8 + e0];
+            if ((lane & 15) < VL) {
+                const float f = s_f[wave][j];
+                const float2 old = first ? make_float2(0.0f, 0.0f) : *o;
+                *o = make_float2(fmaf(old.x, f, x), fmaf(old.y, f, y));
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[j][e] = 0.0f;
+        }
+        wave_lds_fence();
+    };
+    if (n_it > 0) {
+        load_k(0);
+        load_v(0);
+        for (int it = 0; it + 1 < n_it; ++it) {
+            tile(it, std::true_type{});
+            if (it % FL == FL - 1) flush(it == FL - 1);
+        }
+        tile(n_it - 1, std::false_type{});
+        flush(n_it <= FL);
+    } else {
+        for (int i = lane; i < G * D; i += 64) (&s_o[wave][0][0])[i] = 0.0f;
+    }
+    l_sum = add16_f32(l_sum, l_sum);
+    l_sum = add32_f32(l_sum, l_sum);
+    if (lane < G) {
+        s_m[wave][lane] = m;
+        s_l[wave][lane] = l_sum;
+    }
+    __syncthreads();
+    // each wave's factor, and the chunk's maximum and weight sum (wave 0 has a tile)
+    if (tid < NW * G) {
+        const int ww = tid / G, j = tid % G;
+        float mx = s_m[0][j], ls = 0.0f;
+#pragma unroll
+        for (int x = 1; x < NW; ++x) mx = fmaxf(mx, s_m[x][j]);
+        s_f[ww][j] = expf(s_m[ww][j] - mx);
+        if (ww == 0 && j < a.G) {
+#pragma unroll
+            for (int x = 0; x < NW; ++x) ls += expf(s_m[x][j] - mx) * s_l[x][j];
+            float *dst = w.dense_part + ((int64_t)(bh0 + j) * a.n_dense + c) * (D + 2);
+            dst[D] = mx;
+            dst[D + 1] = ls;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < a.G * D; i += NT) {
+        const int j = i / D, e = i % D;
+        float o = 0.0f;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) o += s_f[ww][j] * s_o[ww][j][e];
+        w.dense_part[((int64_t)(bh0 + j) * a.n_dense + c) * (D + 2) + e] = o;
+    }
+}
+
 // k_dense_merge: one block per head; out = sum_c e^(m_c - M) o_c / sum_c e^(m_c - M) l_c
 // with M the largest chunk maximum.  Each wave folds its share of the chunks
 // into a running (maximum, sum, output) with rescaling, so every chunk is read
@@ -2125,7 +2352,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_dense_merge(StepArgs a, Ws w)
     __shared__ float s_m[NW], s_l[NW];
     __shared__ float s_o[NW][D];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, bh = blockIdx.x;
-    const int nch = (int)((a.len + kDenseRows - 1) / kDenseRows);
+    const int nch = (int)((a.len + a.dense_rows - 1) / a.dense_rows);
     const float *part = w.dense_part + (int64_t)bh * a.n_dense * (D + 2);
     float mw = -INFINITY, lw = 0.0f, acc[EPL];
 #pragma unroll
@@ -2499,10 +2726,24 @@ static void score_g(const StepArgs &a, const Geometry &geo, KernelDesc *k)
     }
 }
 
+template <int D>
+static void dense_wave_g(const StepArgs &a, KernelDesc *k)
+{
+    const unsigned blocks = (unsigned)((int64_t)a.B * a.Hkv * ((a.len + a.dense_rows - 1) / a.dense_rows));
+    const void *f;
+    switch (a.G) {
+    case 1: f = (const void *)&k_dense_wave<D, 1>; break;
+    case 2: f = (const void *)&k_dense_wave<D, 2>; break;
+    case 3: case 4: f = (const void *)&k_dense_wave<D, 4>; break;
+    default: f = (const void *)&k_dense_wave<D, 8>; break;
+    }
+    *k = KernelDesc{f, dim3(blocks), dim3(kDenseWaveThreads), 0u, 2};
+}
+
 template <typename T, int D>
 static void dense_g(const StepArgs &a, KernelDesc *k)
 {
-    const unsigned blocks = (unsigned)((int64_t)a.B * a.Hkv * ((a.len + kDenseRows - 1) / kDenseRows));
+    const unsigned blocks = (unsigned)((int64_t)a.B * a.Hkv * ((a.len + a.dense_rows - 1) / a.dense_rows));
     const void *f;
     switch (a.G) {
     case 1: f = (const void *)&k_dense<T, D, 1>; break;
@@ -2530,7 +2771,7 @@ void describe_kernel(int which, int dtype, const StepArgs &a, const Geometry &ge
                         dim3(kScoreThreads), 0u, 3};
         return;
     case KERNEL_DENSE:
-        if (bf) return d64 ? dense_g<uint16_t, 64>(a, k) : dense_g<uint16_t, 128>(a, k);
+        if (bf) return d64 ? dense_wave_g<64>(a, k) : dense_wave_g<128>(a, k);
         return d64 ? dense_g<float, 64>(a, k) : dense_g<float, 128>(a, k);
     case KERNEL_DENSE_MERGE:
         *k = KernelDesc{d64 ? (const void *)&k_dense_merge<64> : (const void *)&k_dense_merge<128>,

@@ -29,10 +29,6 @@ namespace retopk {
 
 namespace {
 
-// 16 bytes as one register value (HIP's uint4 is a struct, whose arrays the compiler
-// kept in scratch memory across the stage loop).
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
 constexpr int kPfWaves = kPfThreads / 64;
 constexpr int kPfQueue = 512;         // accumulator quads a wave queues in LDS
 constexpr int kPfMaxima = 4;          // tile groups whose maxima a wave gathers in LDS
@@ -40,14 +36,6 @@ constexpr int kPfSelThreads = 256;    // k_pf_bound and k_pf_select blocks
 constexpr int kPfBins = 1024;         // value-linear bins
 constexpr int kPfTie = 64;            // entries of the last bin ranked by lane
 constexpr int kPfSegBits = 131072;    // indices per bitmap pass
-
-// Orders LDS accesses of the lanes of one wave (LDS runs them in program order;
-// this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // The larger of two finite scores, without the quieting that fmaxf does first.
 __device__ __forceinline__ float fmax_nan(float x, float y) { return __builtin_elementwise_maximum(x, y); }

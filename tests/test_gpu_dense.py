@@ -66,6 +66,40 @@ def test_full_attention_parity(dtype, d, B, Hq, Hkv, L):
     print(f"max relative error {worst:.3g}", flush=True)
 
 
+@pytest.mark.parametrize("d,B,Hq,Hkv,L", [
+    (128, 1, 28, 4, 255), (128, 1, 3, 1, 257),     # one chunk less a row; a tile of one row
+    (64, 1, 8, 8, 33), (64, 2, 10, 2, 31),         # fewer tiles than waves
+    (128, 1, 24, 8, 20011), (64, 3, 16, 8, 9001),  # several tiles a wave
+])
+def test_full_attention_moving_maximum(d, B, Hq, Hkv, L):
+    """bf16: scores that grow along the rows, so that every tile moves its wave's
+    running maximum and rescales its sums, at the edges of tiles and chunks."""
+    torch = torch_cuda()
+    print(f"full attention, growing scores, d={d} B={B} Hq={Hq} Hkv={Hkv} L={L}", flush=True)
+    rng = np.random.default_rng(L)
+    q = rng.standard_normal((B, Hq, d)).astype(np.float32)
+    lead = rng.standard_normal(d).astype(np.float32)
+    q += 0.5 * lead
+    k = 0.3 * rng.standard_normal((B, Hkv, L, d)).astype(np.float32)
+    k += (4.0 * np.arange(L, dtype=np.float32) / L)[:, None] * lead
+    v = rng.standard_normal((B, Hkv, L, d)).astype(np.float32)
+    raw = [to_bf16_bits(x) for x in (q, k, v)]
+    q, k, v = [bf16_bits_to_f32(x) for x in raw]
+    p = O.Params(B, Hq, Hkv, d, L, 16, 0, 1, 0, 0.5, 0)
+    h = handle_of(p, "bf16")
+    out = torch.full((B, Hq, d), float("nan"), dtype=torch.float32, device="cuda")
+    h.full(*(to_dev(x) for x in raw), L, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    h.close()
+    G = Hq // Hkv
+    for b in range(B):
+        for hq in range(Hq):
+            ref = O.attend(q[b, hq], k[b, hq // G], v[b, hq // G], np.arange(L))
+            # fp32 scores up to about 50: 50 * 2^-24 relative in a weight, a few times over
+            assert rel_err(got[b, hq], ref) <= 2e-5, f"b={b} h={hq}"
+
+
 def test_stream_read_runs():
     """The streaming-read measurement aid reads a buffer and leaves the sink alone
     (the fold of a buffer of equal words is 0, not the sentinel)."""
