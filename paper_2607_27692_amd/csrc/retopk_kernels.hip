@@ -37,6 +37,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <cfloat>
+
 #include <type_traits>
 
 namespace retopk {
@@ -2034,11 +2036,12 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
     };
     load_v(wave * VR);
     __syncthreads();
-    // per head: chunk maximum, then weights exp(s - m) in place and their sum
+    // per head: chunk maximum (at least the lowest finite value, so that a chunk whose
+    // scores are all -inf gets weights of 0), then weights exp(s - m) in place, their sum
     float m[G], l[G];
 #pragma unroll
     for (int j = 0; j < G; ++j) {
-        float x = -INFINITY;
+        float x = -FLT_MAX;
         for (int i = tid; i < nrow; i += NT) x = fmaxf(x, s_sc[j][i]);
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
@@ -2183,7 +2186,9 @@ __global__ __launch_bounds__(kDenseWaveThreads, 2) void k_dense_wave(StepArgs a,
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qb[ks] = __builtin_bit_cast(bf16x8_t, qr[ks * 4 + kq]);
     }
-    float acc[G][8], m = -INFINITY, l = 0.0f;
+    // The maximum starts at the lowest finite value: a tile whose scores are all -inf
+    // (finite keys whose products overflow) then gets weights of 0, not NaN.
+    float acc[G][8], m = -FLT_MAX, l = 0.0f;
 #pragma unroll
     for (int j = 0; j < G; ++j)
 #pragma unroll
@@ -2217,7 +2222,7 @@ __global__ __launch_bounds__(kDenseWaveThreads, 2) void k_dense_wave(StepArgs a,
                 tm = fmaxf(tm, sc[t][i]);
             }
         tm = max_rows_f32(tm);
-        const float mn = fmaxf(m, tm);               // finite: the tile has a row
+        const float mn = fmaxf(m, tm);
         const float f = expf(m - mn);
         m = mn;
         l *= f;

@@ -100,6 +100,41 @@ def test_full_attention_moving_maximum(d, B, Hq, Hkv, L):
             assert rel_err(got[b, hq], ref) <= 2e-5, f"b={b} h={hq}"
 
 
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,L,lo,hi", [
+    ("bf16", 128, 4, 1, 200, 0, 32),          # the first tile of one wave, all there is of it
+    ("bf16", 128, 7, 1, 3000, 256, 288),      # a wave's second tile, after a finite maximum
+    ("bf16", 64, 8, 8, 2500, 1024, 1536),     # whole chunks of 256 rows
+    ("bf16", 64, 2, 2, 700, 690, 700),        # the last, ragged tile
+    ("f32", 64, 4, 2, 2049, 0, 256),          # a whole chunk of 256 rows
+    ("f32", 128, 8, 1, 1500, 1280, 1500),     # the last, ragged chunk
+])
+def test_full_attention_masked_rows(dtype, d, Hq, Hkv, L, lo, hi):
+    """Rows whose finite keys drive the fp32 score to -inf (a mask of nearly the
+    type's lowest value) weigh nothing, also where a whole tile or chunk is such rows."""
+    torch = torch_cuda()
+    print(f"full attention, masked rows, {dtype} d={d} Hq={Hq} Hkv={Hkv} L={L} [{lo}, {hi})", flush=True)
+    rng = np.random.default_rng(L + lo)
+    q = (np.abs(rng.standard_normal((1, Hq, d))) + 0.5).astype(np.float32)
+    k = rng.standard_normal((1, Hkv, L, d)).astype(np.float32)
+    k[:, :, lo:hi] = -3.0e38
+    v = rng.standard_normal((1, Hkv, L, d)).astype(np.float32)
+    if dtype == "bf16":
+        raw = [to_bf16_bits(x) for x in (q, k, v)]
+        q, k, v = [bf16_bits_to_f32(x) for x in raw]
+    else:
+        raw = [q, k, v]
+    h = handle_of(O.Params(1, Hq, Hkv, d, L, 16, 0, 1, 0, 0.5, 0), dtype)
+    out = torch.full((1, Hq, d), float("nan"), dtype=torch.float32, device="cuda")
+    h.full(*(to_dev(x) for x in raw), L, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    h.close()
+    rows = np.concatenate([np.arange(lo), np.arange(hi, L)])
+    for hq in range(Hq):
+        ref = O.attend(q[0, hq], k[0, hq // (Hq // Hkv)], v[0, hq // (Hq // Hkv)], rows)
+        assert rel_err(got[0, hq], ref) <= OUT_TOL[dtype], f"h={hq}"
+
+
 def test_stream_read_runs():
     """The streaming-read measurement aid reads a buffer and leaves the sink alone
     (the fold of a buffer of equal words is 0, not the sentinel)."""
