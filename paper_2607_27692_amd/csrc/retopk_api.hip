@@ -86,38 +86,18 @@ retopk_status validate_config(const retopk_config *c)
     return RETOPK_OK;
 }
 
-// Rows of a full_attention chunk (one block) at length len.
-// bf16: whole 32-row tiles for 240 blocks, at least a tile for each of a block's 8
-// waves.  A CU holds one block (by its registers), so 256 CUs take 240 in one go and a
-// few blocks more start a second one (128K, 8 groups: 95.9 us at 240 and 256, 109 at
-// 260, 118 at 320, 99 at 480; 16K, 4 groups: 15.8 at 224-256, 19.9 above).  240 and not
-// 256 because chunks that start a multiple of 1 MiB apart, give or take 8 KiB, collide
-// on memory channels (1M rows of one group of 8: 101 us, 116 in chunks of 4128 rows;
-// 98 and 112 at 4064), and such sizes are stepped over.  32-bit offsets inside a chunk
-// bound it from above.  f32: the fewest rows with at most four blocks per CU.
-constexpr int kDenseRowsMin = 256, kDenseRowsMax = 65536, kDenseBlocks = 240;
-int dense_rows(const retopk_config &c, int64_t len)
+// Rows of a full_attention chunk (one block) at length len, and the most chunks a KV
+// group has at any length up to max_len.
+static int dense_rows(const retopk_config &c, int64_t len)
 {
     const int64_t groups = (int64_t)c.batch * c.n_kv_heads;
-    if (c.dtype == RETOPK_BF16) {
-        int64_t r = ceil_div(ceil_div(groups * len, kDenseBlocks), 32) * 32;
-        const int64_t off = r * c.head_dim * 2 % (1 << 20);
-        if (r > kDenseRowsMin && (off < 16384 || off > (1 << 20) - 16384)) r += 128;
-        return (int)(r < kDenseRowsMin ? kDenseRowsMin : r > kDenseRowsMax ? kDenseRowsMax : r);
-    }
-    int r = kDenseRowsMin;
-    while (r < kDenseRows && groups * ceil_div(len, r) > 4 * kCUs) r *= 2;
-    return r;
+    return c.dtype == RETOPK_BF16 ? dense_wave_rows(groups, len, c.head_dim) : dense_f32_rows(groups, len);
 }
 
-// The most chunks dense_rows gives any length up to max_len.
-int dense_chunks(const retopk_config &c)
+static int64_t dense_chunks(const retopk_config &c)
 {
     const int64_t groups = (int64_t)c.batch * c.n_kv_heads;
-    const bool bf = c.dtype == RETOPK_BF16;
-    const int64_t spread = ceil_div((bf ? 1 : 4) * kCUs, groups);
-    const int64_t most = ceil_div(c.max_len, bf ? kDenseRowsMax : kDenseRows);
-    return (int)(spread > most ? spread : most);
+    return c.dtype == RETOPK_BF16 ? dense_wave_chunks(groups, c.max_len) : dense_f32_chunks(groups, c.max_len);
 }
 
 StepArgs config_args(const retopk_config &c)
@@ -135,7 +115,7 @@ StepArgs config_args(const retopk_config &c)
     a.W = c.window;
     a.cand_cap = c.r * c.k + c.window;
     a.n_regions = (int)ceil_div(c.max_len, kFilterRows);
-    a.n_dense = dense_chunks(c);
+    a.n_dense = (int)dense_chunks(c);
     a.row_stride = (int64_t)a.n_regions * kFilterRows;
     a.tau = c.tau;
     a.retrieval = c.retrieval;

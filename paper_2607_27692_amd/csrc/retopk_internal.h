@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "retopk.h"
+#include "retopk_plan.h"
 
 namespace retopk {
 
@@ -29,7 +30,6 @@ constexpr int kMaxK = 2048;
 constexpr int kMaxR = 32;
 constexpr int kMaxCache = 4096;
 constexpr int kMaxHeads = 2048;       // B * Hq
-constexpr int kCUs = 256;               // compute units of the chip
 constexpr int kScanBlocksSelect = kCUs; // k_score scan blocks in MODE_SELECT (one per CU)
 constexpr int kScanBlocksExact = 2048;  // k_score scan blocks when every head is exact
 constexpr int64_t kMaxLen = (int64_t)kMaxRegions * kFilterRows;
@@ -181,13 +181,11 @@ struct KernelDesc {
 enum : int { KERNEL_SIM = 0, KERNEL_SCORE = 1, KERNEL_FILTER = 2, KERNEL_FINAL = 3,
               KERNEL_DENSE = 4, KERNEL_DENSE_MERGE = 5 };
 
-// Full (dense) attention: most rows of a chunk block.
-constexpr int kDenseRows = 1024;
+// Full (dense) attention.
 constexpr int kDenseWaveThreads = 512;   // bf16 blocks
 constexpr int kDenseThreads = 512;       // f32 blocks
 constexpr int kMergeThreads = 1024;  // dense merge block: one per query head
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 inline int64_t heads_of(const retopk_config &c) { return (int64_t)c.batch * c.n_q_heads; }
 
@@ -197,7 +195,6 @@ inline int64_t heads_of(const retopk_config &c) { return (int64_t)c.batch * c.n_
 retopk_status validate_config(const retopk_config *c);
 StepArgs config_args(const retopk_config &c);
 void range_split(StepArgs &a);
-int dense_rows(const retopk_config &c, int64_t len);
 Geometry step_geometry(const retopk_config &c, int64_t len, int mode);
 
 // Fills *k for kernel `which` of a step in a.mode (retopk_kernels.hip).

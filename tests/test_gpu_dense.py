@@ -31,6 +31,9 @@ CASES = [
     # the 8-head build at d = 64, bf16 and fp32
     ("bf16", 64, 1, 8, 1, 3000),
     ("f32", 64, 1, 16, 2, 2500),
+    # more KV groups than CUs (several rounds of blocks), and too few for one full round
+    ("bf16", 64, 65, 4, 4, 2100),
+    ("bf16", 128, 67, 4, 2, 2050),
 ]
 
 

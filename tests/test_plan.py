@@ -1,0 +1,99 @@
+"""The launch plans (retopk_plan.h) over whole ranges of sizes, on the CPU: how the
+rows of a call are split over blocks.  The header is plain arithmetic; it is compiled
+here with g++ and called through ctypes."""
+import ctypes as C
+import heapq
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2607_27692_amd", "csrc")
+SOURCE = """
+#include "retopk_plan.h"
+using namespace retopk;
+extern "C" {
+int t_wave_rows(long g, long len, int d) { return dense_wave_rows(g, len, d); }
+long t_wave_chunks(long g, long max_len) { return dense_wave_chunks(g, max_len); }
+int t_f32_rows(long g, long len) { return dense_f32_rows(g, len); }
+long t_f32_chunks(long g, long max_len) { return dense_f32_chunks(g, max_len); }
+}
+"""
+CUS = 256            # compute units, one block each
+FILL = 160           # blocks that saturate HBM together
+ALL_GROUPS = [*range(1, 301), 400, 511, 512, 513, 768, 1024, 1300, 2048]
+LENGTHS = [1, 31, 255, 256, 257, 600, 1024, 2048, 4099, 9000, 16384, 16385, 65536, 131072, 131073,
+           242871, 524288, 1 << 20, (1 << 24) - 1, 1 << 24]
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, lib = d / "plan.cpp", d / "plan.so"
+    src.write_text(SOURCE)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    str(src), "-o", str(lib)], check=True)
+    p = C.CDLL(str(lib))
+    for name, args in (("t_wave_rows", (C.c_long, C.c_long, C.c_int)),
+                       ("t_wave_chunks", (C.c_long, C.c_long)), ("t_f32_rows", (C.c_long, C.c_long)),
+                       ("t_f32_chunks", (C.c_long, C.c_long))):
+        fn = getattr(p, name)
+        fn.argtypes, fn.restype = args, C.c_long
+    return p
+
+
+def makespan(blocks, cus=CUS, fill=FILL):
+    """Time of blocks (their rows, in dispatch order) on `cus` slots that share a
+    bandwidth of one row per unit, which `fill` of them together can use up."""
+    running, t, progress = [], 0.0, 0.0
+    todo = iter(blocks)
+    nxt = next(todo, None)
+    while nxt is not None or running:
+        while nxt is not None and len(running) < cus:
+            heapq.heappush(running, progress + nxt)
+            nxt = next(todo, None)
+        end = heapq.heappop(running)
+        t += (end - progress) * max(len(running) + 1, fill)
+        progress = end
+    return t
+
+
+def chunks(length, rows):
+    return [min(rows, length - r) for r in range(0, length, rows)]
+
+
+# 4096 rows of more than 256 groups: each further round costs a start of some 100 rows,
+# so that the split stops at coarser chunks
+@pytest.mark.parametrize("length, limit", [(4096, 1.3), (16384, 1.12), (131073, 1.12), (1 << 20, 1.12)])
+def test_dense_wave_chunks_are_balanced(plan, length, limit):
+    """bf16 full attention of any number of KV groups that gives every slot work of its
+    own: the time of its blocks is near that of perfectly divisible work."""
+    for groups in ALL_GROUPS:
+        if groups * length < FILL * 2048 or groups * length > 1 << 28:
+            continue
+        for d in (64, 128):
+            rows = plan.t_wave_rows(groups, length, d)
+            t = makespan(chunks(length, rows) * groups)
+            assert t <= limit * groups * length, (
+                f"{groups} groups of {length} rows, d={d}: chunks of {rows}, "
+                f"{groups * -(-length // rows)} blocks, {t / groups / length:.2f} of the ideal time")
+
+
+@pytest.mark.parametrize("kind", ["wave", "f32"])
+def test_dense_chunk_limits(plan, kind):
+    """Chunks stay inside the kernels' limits, and no length up to max_len has more of
+    them than the workspace holds."""
+    for groups in ALL_GROUPS:
+        for i, max_len in enumerate(LENGTHS):
+            room = (plan.t_wave_chunks if kind == "wave" else plan.t_f32_chunks)(groups, max_len)
+            for length in LENGTHS[:i + 1]:
+                if kind == "wave":
+                    for d in (64, 128):
+                        rows = plan.t_wave_rows(groups, length, d)
+                        assert rows % 32 == 0 and 256 <= rows <= 1 << 17
+                        assert -(-length // rows) <= room, (groups, length, max_len)
+                else:
+                    rows = plan.t_f32_rows(groups, length)
+                    assert rows in (256, 512, 1024)
+                    assert -(-length // rows) <= room, (groups, length, max_len)
