@@ -17,7 +17,7 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 constexpr int kDenseRows = 1024;      // f32: most rows of a chunk (its scores sit in LDS)
 constexpr int kDenseRowsMin = 256;    // a 32-row tile for each of a block's 8 waves
-constexpr int kDenseRowsMax = 65536;  // no sum is a chain of more than 128 flushes
+constexpr int kDenseRowsMax = 65536;  // no sum is a chain of more than about 130 flushes
 constexpr int kDenseBlocks = 240;     // bf16 blocks of one round
 constexpr int kDenseFill = 160;       // bf16 blocks that use up the HBM bandwidth together
 constexpr int kDenseRounds = 16;      // rounds of blocks compared
@@ -50,6 +50,18 @@ inline int64_t dense_first_round(int64_t groups, int64_t len)
 // faster by 0.8 % (128K rows, 8 groups: 96.7 us in 240, 97.5 in 248).
 inline int64_t dense_one_round(int64_t groups) { return (groups <= kDenseBlocks ? kDenseBlocks : kCUs) / groups; }
 
+// Chunks that start j MiB apart, give or take j * 8 KiB, meet on the same memory
+// channels, at the ends of the band above all (920 000 rows of one group of 8, d = 128:
+// 101.5 and 100.0 us in chunks of 4064 and 4128 rows, 93.4 in 4032 and 4160; 1 840 000
+// rows at d = 64: 103.2 and 102.8 us in 8128 and 8256, 89.9 in 8320), and inside it at
+// d = 64 with several groups (224 000 rows of 8: 88-90 us, 86 outside).  At most 1.6 %
+// more rows step over it.
+inline bool dense_stride_collides(int64_t bytes)
+{
+    const int64_t j = (bytes + (1 << 19)) >> 20, off = bytes - (j << 20);
+    return j > 0 && (off < 0 ? -off : off) <= j * 8192;
+}
+
 // Rows of a chunk of `groups` KV groups of len rows, d elements a row.
 inline int dense_wave_rows(int64_t groups, int64_t len, int d)
 {
@@ -71,8 +83,7 @@ inline int dense_wave_rows(int64_t groups, int64_t len, int d)
             }
         }
     }
-    const int64_t off = r * d * 2 % (1 << 20);
-    if (r > kDenseRowsMin && (off < 16384 || off > (1 << 20) - 16384)) r += 128;
+    while (dense_stride_collides(r * d * 2)) r += 32;
     return (int)r;
 }
 

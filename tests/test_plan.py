@@ -80,6 +80,18 @@ def test_dense_wave_chunks_are_balanced(plan, length, limit):
                 f"{groups * -(-length // rows)} blocks, {t / groups / length:.2f} of the ideal time")
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_dense_wave_chunks_do_not_collide(plan, d):
+    """Chunks of bf16 rows that start j MiB apart, give or take j * 8 KiB, meet on the
+    same memory channels: no length gets such a chunk size."""
+    for groups in (1, 2, 4, 6, 8, 12, 24, 40, 130, 264):
+        for length in [*range(3000, 1 << 21, 4999), 240 * 4064, 240 * 4128, 30 * 8128, 30 * 8160, 242871]:
+            rows = plan.t_wave_rows(groups, length, d)
+            stride = rows * 2 * d
+            j = (stride + (1 << 19)) >> 20
+            assert j == 0 or abs(stride - (j << 20)) > j * 8192, f"{groups} groups of {length}: chunks of {rows}"
+
+
 @pytest.mark.parametrize("kind", ["wave", "f32"])
 def test_dense_chunk_limits(plan, kind):
     """Chunks stay inside the kernels' limits, and no length up to max_len has more of
