@@ -97,17 +97,22 @@ inline int64_t dense_wave_chunks(int64_t groups, int64_t max_len)
     return most < fine ? most : fine;
 }
 
-// f32: the fewest rows with at most four blocks per CU.
+// f32 (k_dense, up to two blocks a CU): the fewest rows with at most one block per CU, else
+// whole chunks.  More blocks than CUs pay more for their reductions than they win (8
+// groups of d = 128: 4K rows 18.2 us in 128 chunks of 256 rows, 27.3 in 32 of 1024; 16K
+// rows 35.9 in 512 of 256, 31.7 in 256 of 512, 33.0 in 128 of 1024; 64K rows 110.7 in
+// 1024 of 512, 103.4 in 512 of 1024).
 inline int dense_f32_rows(int64_t groups, int64_t len)
 {
     int r = kDenseRowsMin;
-    while (r < kDenseRows && groups * ceil_div(len, r) > 4 * kCUs) r *= 2;
+    while (r < kDenseRows && groups * ceil_div(len, r) > kCUs) r *= 2;
     return r;
 }
 
+// The most chunks a group dense_f32_rows gives any length up to max_len.
 inline int64_t dense_f32_chunks(int64_t groups, int64_t max_len)
 {
-    const int64_t spread = ceil_div(4 * kCUs, groups), most = ceil_div(max_len, kDenseRows);
+    const int64_t spread = ceil_div(kCUs, groups), most = ceil_div(max_len, kDenseRows);
     return spread > most ? spread : most;
 }
 

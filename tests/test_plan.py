@@ -92,6 +92,16 @@ def test_dense_wave_chunks_do_not_collide(plan, d):
             assert j == 0 or abs(stride - (j << 20)) > j * 8192, f"{groups} groups of {length}: chunks of {rows}"
 
 
+def test_dense_f32_chunks_split_only_to_fill(plan):
+    """f32 full attention takes chunks of fewer than 1024 rows only where they still
+    leave at most one block per CU."""
+    for groups in ALL_GROUPS:
+        for length in LENGTHS:
+            rows = plan.t_f32_rows(groups, length)
+            assert rows == 1024 or groups * -(-length // rows) <= CUS, (groups, length, rows)
+            assert rows == 256 or groups * -(-length // (rows // 2)) > CUS, (groups, length, rows)
+
+
 @pytest.mark.parametrize("kind", ["wave", "f32"])
 def test_dense_chunk_limits(plan, kind):
     """Chunks stay inside the kernels' limits, and no length up to max_len has more of
