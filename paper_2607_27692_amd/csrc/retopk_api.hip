@@ -10,7 +10,6 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
-#include <utility>
 #include <vector>
 
 using namespace retopk;
@@ -360,7 +359,6 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     p.qbar = h->w.qbar;
     p.supp = h->w.supp;
     p.supp_cnt = h->w.cnt;
-    bool any_list = false;
     // One launch sequence: positions u0 .. u0 + Uc - 1 (relative to u_first).
     auto sequence = [&](int64_t u0, int64_t Uc, bool dense, float *rows, int64_t stride) -> retopk_status {
         p.U = (int)Uc;
@@ -409,22 +407,21 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
         p.pairs = pairs;
         if ((st = launch(PF_THRESHOLD, KID_FILTER)) != RETOPK_OK) return st;
         if ((st = launch(PF_COLLECT, KID_PF_SCORE)) != RETOPK_OK) return st;
-        any_list = true;
         return launch(PF_SELECT_LIST, KID_FINAL);
     };
     retopk_status st = RETOPK_OK;
-    std::vector<uint32_t> over((size_t)n_eff, 0u);
-    std::vector<std::pair<int64_t, int64_t>> listed;     // position ranges run with lists
+    uint32_t over[kMaxCache];            // n_eff <= C (no allocation that could throw)
+    int64_t listed = n_eff;              // first position run with lists: prefixes only grow
     for (int64_t u0 = 0; u0 < n_eff && st == RETOPK_OK;) {
         const int64_t Uc = n_eff - u0 < U ? n_eff - u0 : U;
         const bool dense = !lists || prefill_len - n + u_first + u0 + 1 < cap;
-        if (!dense) listed.emplace_back(u0, Uc);
+        if (!dense && listed == n_eff) listed = u0;
         // (the rows of a launch of short prefixes: fewer than cap + C <= 2 cap of them)
         st = sequence(u0, Uc, dense, (float *)mem, row_bytes / 4);
         u0 += Uc;
     }
-    if (any_list && st == RETOPK_OK &&
-        hipMemcpyAsync(over.data(), h->pf_mem, (size_t)n_eff * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+    if (listed < n_eff && st == RETOPK_OK &&
+        hipMemcpyAsync(over, h->pf_mem, (size_t)n_eff * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
         st = fail(h);
     // the call returns once the stream has finished its work
     if (hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
@@ -434,21 +431,19 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     float *const rows = fit > 0 ? (float *)mem : h->w.scores;
     const int64_t stride = fit > 0 ? rows16 : base_args(h).row_stride;
     bool again = false;
-    for (const auto &r : listed) {
-        for (int64_t u0 = r.first; u0 < r.first + r.second && st == RETOPK_OK;) {
-            if (!over[(size_t)u0]) {
-                ++u0;
-                continue;
-            }
-            int64_t most = fit > 0 ? fit : 1;
-            if (most > r.first + r.second - u0) most = r.first + r.second - u0;
-            int64_t Uc = 1;
-            for (int64_t i = 1; i < most; ++i)
-                if (over[(size_t)(u0 + i)]) Uc = i + 1;
-            st = sequence(u0, Uc, true, rows, stride);
-            again = true;
-            u0 += Uc;
+    for (int64_t u0 = listed; u0 < n_eff && st == RETOPK_OK;) {
+        if (!over[u0]) {
+            ++u0;
+            continue;
         }
+        int64_t most = fit > 0 ? fit : 1;
+        if (most > n_eff - u0) most = n_eff - u0;
+        int64_t Uc = 1;
+        for (int64_t i = 1; i < most; ++i)
+            if (over[u0 + i]) Uc = i + 1;
+        st = sequence(u0, Uc, true, rows, stride);
+        again = true;
+        u0 += Uc;
     }
     if (again && hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
     h->n_ins += n_eff;
