@@ -122,7 +122,8 @@ typedef struct {
 retopk_status retopk_create(const retopk_config *cfg, retopk_handle *out);
 
 /* Release everything retopk_create allocated: the per-head caches and the
- * preallocated step workspaces of Sec. 3.5.  Waits for the device first.  NULL is
+ * preallocated step workspaces of Sec. 3.5; with the device's last handle, the
+ * prefill workspace too.  Waits for the device first.  NULL is
  * accepted. */
 retopk_status retopk_destroy(retopk_handle h);
 
@@ -133,10 +134,12 @@ retopk_status retopk_destroy(retopk_handle h);
  * decode-step counter.  Queries whose slot a later one overwrites (n > C) only
  * advance the insertion count.  bf16 handles score many positions of every head
  * per launch on the matrix cores (kernel id 7) with up to about 270 MB of device
- * memory, which the handle keeps for its next prefill, and return after the
- * stream has finished that work; when the memory is not available, and for f32,
- * the queries run one position at a time through the decode step's exact path,
- * asynchronously. */
+ * memory, and return after the stream has finished that work, which a stream under
+ * capture refuses (RETOPK_ERR_HIP before anything is queued).  One such workspace a
+ * device is kept for later prefills of any handle until the device's last handle is
+ * destroyed; calls that overlap on other threads allocate their own.  When the memory
+ * is not available, and for f32 or a single query, the queries run one position at a
+ * time through the decode step's exact path, asynchronously. */
 retopk_status retopk_prefill_init(retopk_handle h, const void *q_tail, int32_t n,
                                   const void *k, const void *v, int64_t prefill_len,
                                   void *stream);

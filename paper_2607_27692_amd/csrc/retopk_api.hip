@@ -6,6 +6,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -19,10 +20,11 @@ namespace {
 constexpr int kProfileMaxLaunches = 65536;
 constexpr int kNumKernels = 8;
 // Device memory of the batched prefill (the lists or score rows of U positions of
-// every head), allocated by the handle's first prefill and kept: allocating it per
-// call cost 0.45 ms of an 8.9 ms prefill at 128K, and 17 ms where other handles'
-// memory came and went between the calls.  256 MiB hold 256 positions of 32 heads at
-// K = 512 (32 KiB of list a virtual head and 8 bytes beside it), past which the key reads per launch are no longer what bounds it.
+// every head).  One workspace a device is kept between calls while it has handles:
+// allocating it per call cost 0.45 ms of an 8.9 ms prefill at 128K, and 17 ms where
+// other handles' memory came and went between the calls.  257 MiB hold 256 positions of
+// 32 heads at K = 512 (32 KiB of list a virtual head and 8 bytes beside it), past which
+// the key reads per launch are no longer what bounds it.
 constexpr size_t kPfWorkspaceBytes = (size_t)257 << 20;
 // retopk_score is the scoring kernel of a decode step that selects (candidate
 // blocks beside the scans of fallback heads); retopk_scan is the same kernel
@@ -50,8 +52,6 @@ struct retopk_handle_s {
     hipStream_t last_stream = nullptr;
     bool has_last = false;             // a call has queued work on last_stream
     hipEvent_t order_ev = nullptr;     // orders a call on a new stream after the last
-    void *pf_mem = nullptr;            // batched prefill workspace
-    size_t pf_bytes = 0;
     // host-side counters (paths decided on the host)
     uint64_t steps = 0, head_steps = 0, refresh = 0, cold = 0, host_scans = 0;
     // profiling
@@ -294,6 +294,82 @@ void prefill_grid(PfArgs &p, int64_t cols, int64_t groups, int64_t rows)
     p.pairs = (int)(groups * p.chunks);
 }
 
+// The prefill workspaces kept between calls: at most one a device, held while the device
+// has handles.  A call takes it (or allocates another while a call on another thread has
+// it) and puts it back once the stream has finished with it, so that handles, threads
+// and streams never share it; of two that come back the larger stays.
+struct PfBlock {
+    void *mem;
+    size_t bytes;
+};
+struct PfPool {
+    std::atomic<PfBlock *> idle{nullptr};
+    std::atomic<int64_t> handles{0};
+};
+constexpr int kPfDevices = 64;            // devices past it allocate per call
+PfPool g_pf[kPfDevices];
+
+PfPool *pool_of(int device) { return device >= 0 && device < kPfDevices ? &g_pf[device] : nullptr; }
+
+void free_block(PfBlock *b)
+{
+    if (!b) return;
+    (void)hipFree(b->mem);                // waits for the device
+    delete b;
+}
+
+void keep_workspace(int device)
+{
+    if (PfPool *p = pool_of(device)) p->handles.fetch_add(1);
+}
+
+void drop_workspace(int device)
+{
+    PfPool *p = pool_of(device);
+    if (p && p->handles.fetch_sub(1) == 1) free_block(p->idle.exchange(nullptr));
+}
+
+// One call's workspace (the device is current); mem is null when there is none to be had.
+struct PfWorkspace {
+    PfPool *pool;
+    PfBlock *block = nullptr;
+    void *mem = nullptr;
+    size_t bytes = 0;
+    bool idle = false;                    // set once no work of the call is left on it
+
+    PfWorkspace(int device, size_t want) : pool(pool_of(device))
+    {
+        if (pool) block = pool->idle.exchange(nullptr);
+        if (block && block->bytes < want) {
+            free_block(block);
+            block = nullptr;
+        }
+        if (!block) {
+            block = new (std::nothrow) PfBlock{nullptr, want};
+            if (!block) return;
+            if (hipMalloc(&block->mem, want) != hipSuccess) {
+                (void)hipGetLastError();
+                delete block;
+                block = nullptr;
+                return;
+            }
+        }
+        mem = block->mem;
+        bytes = block->bytes;
+    }
+    ~PfWorkspace()
+    {
+        if (block && pool && idle) {
+            PfBlock *other = pool->idle.exchange(block);
+            if (other && other->bytes > block->bytes) other = pool->idle.exchange(other);
+            block = other;
+        }
+        free_block(block);
+    }
+    PfWorkspace(const PfWorkspace &) = delete;
+    PfWorkspace &operator=(const PfWorkspace &) = delete;
+};
+
 // Batched prefill initialisation (bf16): positions u_first .. n-1 of q_tail in
 // launch sequences of U positions each (see retopk_prefill.hip).  A launch whose
 // shortest prefix is at least `cap` rows long collects lists under a bound of the
@@ -329,19 +405,10 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     const size_t head = ((size_t)n_eff * 4 + 255) / 256 * 256;
     const bool lists = row_bytes == cap * 8 && prefill_len > cap;
     const size_t body = (size_t)(per_u * U);
-    if (h->pf_bytes < head + body) {
-        if (h->pf_mem) (void)hipFree(h->pf_mem);    // its last prefill has finished
-        h->pf_mem = nullptr;
-        h->pf_bytes = 0;
-        if (hipMalloc(&h->pf_mem, head + body) != hipSuccess) {
-            (void)hipGetLastError();
-            h->pf_mem = nullptr;
-            return RETOPK_ERR_OOM;
-        }
-        h->pf_bytes = head + body;
-    }
-    const size_t room = h->pf_bytes - head;
-    char *mem = (char *)h->pf_mem + head;
+    PfWorkspace ws(h->device, head + body);
+    if (!ws.mem) return RETOPK_ERR_OOM;
+    const size_t room = ws.bytes - head;
+    char *mem = (char *)ws.mem + head;
 
     PfArgs p{};
     p.B = c.batch;
@@ -365,7 +432,7 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
         p.q = (const uint16_t *)(q_tail + (size_t)(u_first + u0) * c.head_dim * es);
         p.len0 = prefill_len - n + u_first + u0 + 1;
         p.insert_slot = (int32_t)((h->n_ins + u0) % C);
-        p.overflow = (uint32_t *)h->pf_mem + u0;
+        p.overflow = (uint32_t *)ws.mem + u0;
         const int64_t len_max = p.len0 + Uc - 1;
         const int64_t vheads = BH * Uc;
         prefill_grid(p, h->G * Uc, groups, len_max);
@@ -421,10 +488,11 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
         u0 += Uc;
     }
     if (listed < n_eff && st == RETOPK_OK &&
-        hipMemcpyAsync(over, h->pf_mem, (size_t)n_eff * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+        hipMemcpyAsync(over, ws.mem, (size_t)n_eff * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
         st = fail(h);
     // the call returns once the stream has finished its work
     if (hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
+    ws.idle = st == RETOPK_OK;
     // The overflowed positions again, with score rows: as many at a time as fit, or
     // one in the handle's own score rows.
     const int64_t fit = (int64_t)(room / ((size_t)BH * (size_t)rows16 * 4));
@@ -445,7 +513,10 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
         again = true;
         u0 += Uc;
     }
-    if (again && hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
+    if (again) {
+        if (hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
+        ws.idle = st == RETOPK_OK;
+    }
     h->n_ins += n_eff;
     return st;
 }
@@ -515,6 +586,7 @@ retopk_status retopk_create(const retopk_config *cfg, retopk_handle *out)
         delete h;
         return RETOPK_ERR_HIP;
     }
+    keep_workspace(h->device);
     const int64_t BH = heads_of(*cfg);
     const int64_t C = cfg->cache_cap, D = cfg->head_dim, K = cfg->k, L = cfg->max_len;
     Ws &w = h->w;
@@ -554,7 +626,7 @@ retopk_status retopk_destroy(retopk_handle h)
     (void)hipSetDevice(h->device);
     if (!h->allocs.empty()) (void)hipDeviceSynchronize();
     for (void *p : h->allocs) (void)hipFree(p);
-    if (h->pf_mem) (void)hipFree(h->pf_mem);
+    drop_workspace(h->device);
     for (hipEvent_t e : h->ev) (void)hipEventDestroy(e);
     if (h->order_ev) (void)hipEventDestroy(h->order_ev);
     delete h;
@@ -653,13 +725,20 @@ retopk_status retopk_prefill_init(retopk_handle h, const void *q_tail, int32_t n
     if (c.cache_cap == 0 || n == 0) return RETOPK_OK;
     hipStream_t s = (hipStream_t)stream;
     if (hipSetDevice(h->device) != hipSuccess) return fail(h);
-    if (order_after_last(h, s) != RETOPK_OK) return RETOPK_ERR_HIP;
     // Positions whose slot a later prompt-tail query overwrites (n > C) only
     // advance the insertion count.
     const int32_t u_first = n > c.cache_cap ? n - c.cache_cap : 0;
+    const bool batched = c.dtype == RETOPK_BF16 && n - u_first > 1;
+    if (batched) {
+        // it waits for its own work, which a capture cannot
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &capturing) != hipSuccess) (void)hipGetLastError();
+        if (capturing != hipStreamCaptureStatusNone) return RETOPK_ERR_HIP;
+    }
+    if (order_after_last(h, s) != RETOPK_OK) return RETOPK_ERR_HIP;
     h->n_ins += u_first;
     set_last(h, s);
-    if (c.dtype == RETOPK_BF16 && n - u_first > 1) {
+    if (batched) {
         const retopk_status st = prefill_batched(h, (const char *)q_tail, n, u_first, k, prefill_len, s);
         if (st != RETOPK_ERR_OOM) return st;
     }

@@ -12,6 +12,7 @@ import pytest
 
 from gpu_harness import Tally, check_selection, handle_of, params_of, to_dev, torch_cuda
 from oracle import oracle as O
+from paper_2607_27692_amd import retopk as R
 from paper_2607_27692_amd.inputs import WORKLOADS, make_inputs
 
 pytestmark = pytest.mark.gpu
@@ -209,3 +210,100 @@ def test_prefill_batched_bounds_and_lists(label, change, equal):
     _compare_states(p, gst, orc.get_state(), list(range(p.heads)), inp.q_tail, kf, w.prompt_len,
                     tally)
     print(tally, flush=True)
+
+
+def _workspace_case(seed):
+    """A layer whose batched prefill takes the whole workspace (32 heads x 256 positions)."""
+    torch = torch_cuda()
+    w = WORKLOADS["16k"].with_(prompt_len=9000, cache_cap=256)
+    gen = torch.Generator("cuda")
+    gen.manual_seed(seed)
+    k = torch.randn((1, w.n_kv_heads, w.max_len, w.head_dim), generator=gen, device="cuda").bfloat16()
+    q = torch.randn((1, w.n_q_heads, w.cache_cap, w.head_dim), generator=gen, device="cuda").bfloat16()
+    return w, k, q
+
+
+def test_prefill_workspace_is_shared():
+    """Handles of one device (layers of one model) keep one prefill workspace between
+    them, and none once the last handle is gone."""
+    torch = torch_cuda()
+    print("prefill workspace of several handles", flush=True)
+    w, k, q = _workspace_case(1)
+    p = params_of(w)
+    free = lambda: torch.cuda.mem_get_info()[0]  # noqa: E731
+    before = free()
+    handles = [handle_of(p, w.dtype) for _ in range(4)]
+    held = before - free()                      # the handles' own memory
+    kept = []
+    for h in handles:
+        h.prefill_init(q, w.cache_cap, k, k, w.prompt_len)
+        kept.append(before - free() - held)
+    assert kept[0] <= 300 << 20
+    assert kept[-1] <= kept[0] + (16 << 20), f"{[x >> 20 for x in kept]} MiB kept"
+    states = [h.get_state() for h in handles]
+    for st in states[1:]:
+        assert all(np.array_equal(st[x], states[0][x]) for x in ("qbar", "supp", "cnt"))
+    for h in handles:
+        h.close()
+    assert before - free() <= 32 << 20, f"{(before - free()) >> 20} MiB left"
+
+
+def test_prefill_on_two_threads():
+    """Two threads prefill their own handles on their own streams, over and over: each
+    gets what it gets alone."""
+    import threading
+    torch = torch_cuda()
+    print("prefill on two threads", flush=True)
+    cases = [_workspace_case(s) for s in (2, 3)]
+    want, got, errors = [], [None, None], []
+    for w, k, q in cases:
+        with handle_of(params_of(w), w.dtype) as h:
+            h.prefill_init(q, w.cache_cap, k, k, w.prompt_len)
+            want.append(h.get_state())
+    torch.cuda.synchronize()
+
+    def work(i):
+        try:
+            w, k, q = cases[i]
+            stream = torch.cuda.Stream()
+            with handle_of(params_of(w), w.dtype) as h:
+                for _ in range(8):
+                    h.prefill_init(q, w.cache_cap, k, k, w.prompt_len, stream=stream)
+                got[i] = h.get_state()
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for i in range(2):
+        assert all(np.array_equal(got[i][x], want[i][x]) for x in ("qbar", "supp", "cnt")), i
+
+
+def test_prefill_under_capture_is_refused():
+    """A batched prefill waits for its own work, so a capturing stream is refused before
+    anything is recorded; the capture and the handle stay usable."""
+    torch = torch_cuda()
+    print("prefill under capture", flush=True)
+    w, k, q = _workspace_case(4)
+    with handle_of(params_of(w), w.dtype) as h:
+        h.prefill_init(q, w.cache_cap, k, k, w.prompt_len)
+        want = h.get_state()
+        x = torch.zeros(8, device="cuda")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            with pytest.raises(R.RetopkError) as e:
+                h.prefill_init(q, w.cache_cap, k, k, w.prompt_len)
+            x.add_(1.0)
+        assert e.value.code == -4
+        for i in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert (x == i + 1).all()
+        h.prefill_init(q, w.cache_cap, k, k, w.prompt_len)
+        got = h.get_state()
+        assert all(np.array_equal(got[x], want[x]) for x in ("qbar", "supp", "cnt"))
