@@ -19,13 +19,6 @@ namespace {
 
 constexpr int kProfileMaxLaunches = 65536;
 constexpr int kNumKernels = 8;
-// Device memory of the batched prefill (the lists or score rows of U positions of
-// every head).  One workspace a device is kept between calls while it has handles:
-// allocating it per call cost 0.45 ms of an 8.9 ms prefill at 128K, and 17 ms where
-// other handles' memory came and went between the calls.  257 MiB hold 256 positions of
-// 32 heads at K = 512 (32 KiB of list a virtual head and 8 bytes beside it), past which
-// the key reads per launch are no longer what bounds it.
-constexpr size_t kPfWorkspaceBytes = (size_t)257 << 20;
 // retopk_score is the scoring kernel of a decode step that selects (candidate
 // blocks beside the scans of fallback heads); retopk_scan is the same kernel
 // built for steps where every head takes the full-history scan.
@@ -274,26 +267,6 @@ retopk_status run_step(retopk_handle h, const StepArgs &a, int mode, hipStream_t
     return RETOPK_OK;
 }
 
-// Grid of k_pf_scan for `cols` virtual queries per KV group over the rows of
-// `groups` KV groups: as many waves side by side along the queries as there are
-// 128-query tiles (up to the block's 8), and key chunks for about one block per CU
-// (a CU holds one, by its registers; each block first loads its queries, 256 KB, so
-// two shorter blocks one after the other cost 4 % more), no shorter than 512 rows.
-void prefill_grid(PfArgs &p, int64_t cols, int64_t groups, int64_t rows)
-{
-    const int64_t tiles = ceil_div(cols, kPfWaveCols);
-    p.wc = 1;
-    while (p.wc < kPfThreads / 64 && p.wc < tiles) p.wc *= 2;
-    p.col_blocks = (int)ceil_div(tiles, p.wc);
-    const int64_t want = ceil_div(kCUs, groups * p.col_blocks);
-    const int64_t most = ceil_div(rows, 512);
-    const int64_t n = want < most ? want : most;
-    const int64_t unit = 16 * (kPfThreads / 64 / p.wc);
-    p.chunk_rows = ceil_div(ceil_div(rows, n), unit) * unit;
-    p.chunks = (int)ceil_div(rows, p.chunk_rows);
-    p.pairs = (int)(groups * p.chunks);
-}
-
 // The prefill workspaces kept between calls: at most one a device, held while the device
 // has handles.  A call takes it (or allocates another while a call on another thread has
 // it) and puts it back once the stream has finished with it, so that handles, threads
@@ -383,32 +356,12 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     const int64_t BH = heads_of(c), C = c.cache_cap, K = c.k;
     const int64_t n_eff = n - u_first, groups = (int64_t)c.batch * c.n_kv_heads;
     const size_t es = elem_size(c);
-    // List capacity: eight times K, four times what the bound is expected to leave.
-    const int64_t cap = 8 * K > kPfMinList ? 8 * K : kPfMinList;
-    const int64_t rows16 = ceil_div(prefill_len, 16) * 16;
-    // Bytes per virtual head: a list of cap ranks, which also holds its group maxima
-    // (at most 8 K floats) or a score row of up to 2 cap rows; its count and bound.
-    const int64_t row_bytes = rows16 * 4 < cap * 8 ? rows16 * 4 : cap * 8;
-    const int64_t per_u = BH * (row_bytes + 8);
-    int64_t U = (int64_t)kPfWorkspaceBytes / per_u;
-    // whole 128-query tiles where the budget allows
-    int gcd = h->G, m = kPfWaveCols;
-    while (m) {
-        const int r = gcd % m;
-        gcd = m;
-        m = r;
-    }
-    const int64_t unit = kPfWaveCols / gcd;
-    if (U >= unit) U -= U % unit;
-    U = U < 1 ? 1 : (U > n_eff ? n_eff : U);
-    // overflow words of every position, then the virtual heads' memory
-    const size_t head = ((size_t)n_eff * 4 + 255) / 256 * 256;
-    const bool lists = row_bytes == cap * 8 && prefill_len > cap;
-    const size_t body = (size_t)(per_u * U);
-    PfWorkspace ws(h->device, head + body);
+    const PrefillPlan plan = prefill_plan(BH, h->G, K, n_eff, prefill_len);
+    const int64_t cap = plan.cap, U = plan.positions;
+    PfWorkspace ws(h->device, (size_t)plan.bytes);
     if (!ws.mem) return RETOPK_ERR_OOM;
-    const size_t room = ws.bytes - head;
-    char *mem = (char *)ws.mem + head;
+    const size_t room = ws.bytes - (size_t)plan.head_bytes;
+    char *mem = (char *)ws.mem + plan.head_bytes;
 
     PfArgs p{};
     p.B = c.batch;
@@ -435,7 +388,12 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
         p.overflow = (uint32_t *)ws.mem + u0;
         const int64_t len_max = p.len0 + Uc - 1;
         const int64_t vheads = BH * Uc;
-        prefill_grid(p, h->G * Uc, groups, len_max);
+        const PrefillGrid grid = prefill_grid(h->G * Uc, groups, len_max);
+        p.wc = grid.wc;
+        p.col_blocks = grid.col_blocks;
+        p.chunks = grid.chunks;
+        p.chunk_rows = grid.chunk_rows;
+        p.pairs = (int)(groups * grid.chunks);
         void *args[1] = {&p};
         auto launch = [&](int which, int kid) -> retopk_status {
             KernelDesc d;
@@ -481,10 +439,10 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     int64_t listed = n_eff;              // first position run with lists: prefixes only grow
     for (int64_t u0 = 0; u0 < n_eff && st == RETOPK_OK;) {
         const int64_t Uc = n_eff - u0 < U ? n_eff - u0 : U;
-        const bool dense = !lists || prefill_len - n + u_first + u0 + 1 < cap;
+        const bool dense = !plan.lists || prefill_len - n + u_first + u0 + 1 < cap;
         if (!dense && listed == n_eff) listed = u0;
         // (the rows of a launch of short prefixes: fewer than cap + C <= 2 cap of them)
-        st = sequence(u0, Uc, dense, (float *)mem, row_bytes / 4);
+        st = sequence(u0, Uc, dense, (float *)mem, plan.row_bytes / 4);
         u0 += Uc;
     }
     if (listed < n_eff && st == RETOPK_OK &&
@@ -495,9 +453,9 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     ws.idle = st == RETOPK_OK;
     // The overflowed positions again, with score rows: as many at a time as fit, or
     // one in the handle's own score rows.
-    const int64_t fit = (int64_t)(room / ((size_t)BH * (size_t)rows16 * 4));
+    const int64_t fit = (int64_t)(room / ((size_t)BH * (size_t)plan.rows16 * 4));
     float *const rows = fit > 0 ? (float *)mem : h->w.scores;
-    const int64_t stride = fit > 0 ? rows16 : base_args(h).row_stride;
+    const int64_t stride = fit > 0 ? plan.rows16 : base_args(h).row_stride;
     bool again = false;
     for (int64_t u0 = listed; u0 < n_eff && st == RETOPK_OK;) {
         if (!over[u0]) {

@@ -34,11 +34,6 @@ constexpr int kScanBlocksSelect = kCUs; // k_score scan blocks in MODE_SELECT (o
 constexpr int kScanBlocksExact = 2048;  // k_score scan blocks when every head is exact
 constexpr int64_t kMaxLen = (int64_t)kMaxRegions * kFilterRows;
 
-// Batched prefill initialisation (bf16, retopk_prefill.hip).
-constexpr int kPfThreads = 512;
-constexpr int kPfWaveCols = 128;      // virtual queries held by one wave
-constexpr int kPfMinList = 4096;      // smallest list capacity of a virtual head
-
 // Step modes.  SELECT runs the per-head path rule on the device; the others take
 // the exact path for every head.
 enum Mode : int {

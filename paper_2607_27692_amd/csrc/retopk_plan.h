@@ -116,4 +116,98 @@ inline int64_t dense_f32_chunks(int64_t groups, int64_t max_len)
     return spread > most ? spread : most;
 }
 
+// ---------------------------------------------------------------------------
+// Batched prefill initialisation (bf16, retopk_prefill.hip)
+// ---------------------------------------------------------------------------
+
+constexpr int kPfThreads = 512;
+constexpr int kPfWaveCols = 128;      // virtual queries held by one wave
+constexpr int kPfMinList = 4096;      // smallest list capacity of a virtual head
+// Device memory of the batched prefill (the lists or score rows of U positions of
+// every head).  One workspace a device is kept between calls while it has handles:
+// allocating it per call cost 0.45 ms of an 8.9 ms prefill at 128K, and 17 ms where
+// other handles' memory came and went between the calls.  257 MiB hold 256 positions of
+// 32 heads at K = 512 (32 KiB of list a virtual head and 8 bytes beside it), past which
+// the key reads per launch are no longer what bounds it.
+constexpr int64_t kPfWorkspaceBytes = (int64_t)257 << 20;
+struct PrefillPlan {
+    int64_t cap;               // list capacity of a virtual head
+    int64_t rows16;            // rows of a score row: the prompt in whole tiles
+    int64_t row_bytes;         // memory of a virtual head's list or score row
+    int64_t positions;         // positions a launch takes
+    bool lists;                // launches keep lists, else score rows
+    int64_t head_bytes, bytes; // words per position; the whole workspace
+};
+
+// n positions of `heads` query heads, G to a KV group, of a prompt of prefill_len rows.
+inline PrefillPlan prefill_plan(int64_t heads, int G, int64_t K, int64_t n, int64_t prefill_len)
+{
+    PrefillPlan p;
+    // eight times K, four times what the bound is expected to leave
+    p.cap = 8 * K > kPfMinList ? 8 * K : kPfMinList;
+    p.rows16 = ceil_div(prefill_len, 16) * 16;
+    // A list of cap ranks, which also holds its group maxima (at most 8 K floats), or a
+    // score row of up to 2 cap rows; beside it the count and the bound.
+    p.row_bytes = p.rows16 * 4 < p.cap * 8 ? p.rows16 * 4 : p.cap * 8;
+    p.lists = p.row_bytes == p.cap * 8 && prefill_len > p.cap;
+    const int64_t per_u = heads * (p.row_bytes + 8);
+    int64_t U = kPfWorkspaceBytes / per_u;
+    // whole 128-query tiles where the budget allows
+    int gcd = G, m = kPfWaveCols;
+    while (m) {
+        const int r = gcd % m;
+        gcd = m;
+        m = r;
+    }
+    const int64_t unit = kPfWaveCols / gcd;
+    if (U >= unit) U -= U % unit;
+    p.positions = U < 1 ? 1 : (U > n ? n : U);
+    // overflow words of every position, then the virtual heads' memory
+    p.head_bytes = ceil_div(n * 4, 256) * 256;
+    p.bytes = p.head_bytes + per_u * p.positions;
+    return p;
+}
+
+// Grid of k_pf_scan: blocks of wc * 128 virtual queries times a chunk of key rows.
+struct PrefillGrid {
+    int wc, col_blocks, chunks;
+    int64_t chunk_rows;
+};
+
+// `cols` virtual queries per KV group over the rows of `groups` KV groups: as many waves
+// side by side along the queries as there are 128-query tiles (up to the block's 8), and
+// key chunks, no shorter than 512 rows, for whole rounds of blocks.  A CU holds one
+// block (by its registers), a (KV group, chunk) pair's blocks run on one XCD of 32 CUs,
+// and a few blocks too many cost a round (12/2 heads, 128K rows: 757 us in 258
+// blocks of 43 chunks, 491 in 240 of 40).  Of 16 numbers of rounds the shortest
+// counts; a block's start (its queries, 256 KB) costs as much as 170 rows (two rounds of
+// half the rows took 4 % longer than one).
+inline PrefillGrid prefill_grid(int64_t cols, int64_t groups, int64_t rows)
+{
+    constexpr int64_t kXcds = 8, kStartRows = 170, kRounds = 16;
+    PrefillGrid g;
+    const int64_t tiles = ceil_div(cols, kPfWaveCols);
+    g.wc = 1;
+    while (g.wc < kPfThreads / 64 && g.wc < tiles) g.wc *= 2;
+    const int64_t cb = ceil_div(tiles, g.wc), most = ceil_div(rows, 512);
+    g.col_blocks = (int)cb;
+    const int64_t unit = 16 * (kPfThreads / 64 / g.wc);
+    const int64_t slots = kCUs / kXcds;             // of an XCD
+    const int64_t m0 = ceil_div(ceil_div(groups, kXcds) * cb, slots);
+    int64_t best = -1;
+    for (int64_t m = m0; m < m0 + kRounds; ++m) {
+        int64_t n = slots * m / cb * kXcds / groups;
+        if (n > most) n = most;
+        const int64_t chunk = ceil_div(ceil_div(rows, n), unit) * unit;
+        const int64_t pairs = groups * ceil_div(rows, chunk);
+        const int64_t cost = ceil_div(ceil_div(pairs, kXcds) * cb, slots) * (chunk + kStartRows);
+        if (best < 0 || cost < best) {
+            best = cost;
+            g.chunk_rows = chunk;
+        }
+    }
+    g.chunks = (int)ceil_div(rows, g.chunk_rows);
+    return g;
+}
+
 }  // namespace retopk

@@ -18,6 +18,18 @@ int t_wave_rows(long g, long len, int d) { return dense_wave_rows(g, len, d); }
 long t_wave_chunks(long g, long max_len) { return dense_wave_chunks(g, max_len); }
 int t_f32_rows(long g, long len) { return dense_f32_rows(g, len); }
 long t_f32_chunks(long g, long max_len) { return dense_f32_chunks(g, max_len); }
+void t_prefill_plan(long heads, int G, long K, long n, long len, long *out)
+{
+    const PrefillPlan p = prefill_plan(heads, G, K, n, len);
+    const long v[] = {p.cap, p.rows16, p.row_bytes, p.positions, p.lists, p.head_bytes, p.bytes};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
+void t_prefill_grid(long cols, long groups, long rows, long *out)
+{
+    const PrefillGrid g = prefill_grid(cols, groups, rows);
+    const long v[] = {g.wc, g.col_blocks, g.chunks, g.chunk_rows};
+    for (int i = 0; i < 4; ++i) out[i] = v[i];
+}
 }
 """
 CUS = 256            # compute units, one block each
@@ -40,6 +52,19 @@ def plan(tmp_path_factory):
                        ("t_f32_chunks", (C.c_long, C.c_long))):
         fn = getattr(p, name)
         fn.argtypes, fn.restype = args, C.c_long
+    out = (C.c_long * 8)()
+    p.t_prefill_plan.argtypes = (C.c_long, C.c_int, C.c_long, C.c_long, C.c_long, C.c_void_p)
+    p.t_prefill_grid.argtypes = (C.c_long, C.c_long, C.c_long, C.c_void_p)
+
+    def prefill_plan(*args):
+        p.t_prefill_plan(*args, out)
+        return dict(zip(("cap", "rows16", "row_bytes", "positions", "lists", "head_bytes", "bytes"), out))
+
+    def prefill_grid(*args):
+        p.t_prefill_grid(*args, out)
+        return dict(zip(("wc", "col_blocks", "chunks", "chunk_rows"), out))
+
+    p.prefill_plan, p.prefill_grid = prefill_plan, prefill_grid
     return p
 
 
@@ -119,3 +144,48 @@ def test_dense_chunk_limits(plan, kind):
                     rows = plan.t_f32_rows(groups, length)
                     assert rows in (256, 512, 1024)
                     assert -(-length // rows) <= room, (groups, length, max_len)
+
+
+START_ROWS = 170     # what the start of a k_pf_scan block costs, in rows
+
+
+# at 16K rows, chunks for another round would be shorter than their start is worth
+@pytest.mark.parametrize("rows, limit", [(16384, 1.25), (65536, 1.12), (131072, 1.12), (131600, 1.12),
+                                         (1 << 20, 1.12)])
+def test_prefill_grid_is_balanced(plan, rows, limit):
+    """k_pf_scan for any number of KV groups and virtual queries: the time of its blocks,
+    placed on the 8 XCDs in turn, is near that of evenly divided work."""
+    for groups in [*range(1, 41), 56, 72, 96, 130, 200, 256, 257, 264, 400, 2048]:
+        for cols in (1, 16, 128, 130, 256, 640, 1024, 1025, 1792, 3072, 4096, 32768):
+            g = plan.prefill_grid(cols, groups, rows)
+            work = groups * g["col_blocks"] * rows
+            if work < CUS * 2048 or work > 1 << 25:
+                continue
+            pairs = groups * g["chunks"]
+            sizes = chunks(rows, g["chunk_rows"])
+            assert len(sizes) == g["chunks"] and g["wc"] * g["col_blocks"] * 128 >= cols
+            worst = 0.0
+            for xcd in range(8):
+                blocks = [sizes[pair % g["chunks"]] + START_ROWS for pair in range(xcd, pairs, 8)
+                          for _ in range(g["col_blocks"])]
+                worst = max(worst, makespan(blocks, CUS // 8, CUS // 8) * 8)
+            assert worst <= limit * (work + CUS * START_ROWS), (
+                f"{groups} groups, {cols} queries, {rows} rows: {g}, {worst / work:.2f} of the ideal time")
+
+
+def test_prefill_plan_limits(plan):
+    """Workspaces are bounded, and a launch's lists or score rows fit them."""
+    for heads, G in ((1, 1), (4, 4), (28, 7), (32, 4), (40, 5), (64, 1), (2048, 8)):
+        for K in (1, 64, 512, 513, 2048):
+            for n in (2, 32, 512, 4096):
+                for length in (n, 4095, 4096, 8175, 8176, 8192, 16384, 32768, 131072, 1 << 24):
+                    if length < n:
+                        continue
+                    p = plan.prefill_plan(heads, G, K, n, length)
+                    assert 1 <= p["positions"] <= n
+                    assert p["bytes"] - p["head_bytes"] == heads * (p["row_bytes"] + 8) * p["positions"]
+                    assert p["bytes"] <= max(258 << 20, (heads * (p["row_bytes"] + 8)) + (1 << 20))
+                    if p["lists"]:
+                        assert p["row_bytes"] == 8 * p["cap"] and p["cap"] >= 8 * K
+                    else:
+                        assert p["row_bytes"] >= 4 * p["rows16"]
