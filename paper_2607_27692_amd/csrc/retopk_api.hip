@@ -343,11 +343,17 @@ struct PfWorkspace {
     PfWorkspace &operator=(const PfWorkspace &) = delete;
 };
 
+// Runs of the lists that overflowed, each under a bound that the one before left, before
+// their positions take score rows.  Of keys without ties a run leaves about an eighth of
+// what overflowed; of equal scores it keeps the lower indices, and the list holds what
+// came first from every key chunk, so that a few runs reach the K lowest.
+constexpr int kPfReruns = 3;
+
 // Batched prefill initialisation (bf16): positions u_first .. n-1 of q_tail in
-// launch sequences of U positions each (see retopk_prefill.hip).  A launch whose
-// shortest prefix is at least `cap` rows long collects lists under a bound of the
-// K-th largest score; a shorter one stores its score rows.  Positions in which a
-// list overflowed are run again with score rows.  Returns RETOPK_ERR_OOM, having
+// launch sequences of U positions each (see retopk_prefill.hip).  Prompts of at least
+// two lists' rows collect lists under a bound of the K-th largest score; shorter ones
+// store their score rows.  Lists that overflowed are run again under a higher bound, and
+// the positions in which one still does with score rows.  Returns RETOPK_ERR_OOM, having
 // launched nothing, when the workspace cannot be allocated.
 retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, int32_t u_first,
                               const void *k, int64_t prefill_len, hipStream_t s)
@@ -360,8 +366,8 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     const int64_t cap = plan.cap, U = plan.positions;
     PfWorkspace ws(h->device, (size_t)plan.bytes);
     if (!ws.mem) return RETOPK_ERR_OOM;
-    const size_t room = ws.bytes - (size_t)plan.head_bytes;
-    char *mem = (char *)ws.mem + plan.head_bytes;
+    char *mem = (char *)ws.mem;
+    uint32_t *const words = (uint32_t *)(mem + plan.over_at);
 
     PfArgs p{};
     p.B = c.batch;
@@ -379,13 +385,20 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     p.qbar = h->w.qbar;
     p.supp = h->w.supp;
     p.supp_cnt = h->w.cnt;
-    // One launch sequence: positions u0 .. u0 + Uc - 1 (relative to u_first).
-    auto sequence = [&](int64_t u0, int64_t Uc, bool dense, float *rows, int64_t stride) -> retopk_status {
+    // One launch sequence: positions u0 .. u0 + Uc - 1 (relative to u_first) with lists
+    // under a bound from a sample of the keys, with the lists that overflowed under the
+    // bounds they left, or with score rows.
+    enum Run { LISTS, AGAIN, ROWS };
+    float *rows = (float *)mem;
+    int64_t stride = plan.rows16;
+    auto sequence = [&](int64_t u0, int64_t Uc, Run run) -> retopk_status {
         p.U = (int)Uc;
         p.q = (const uint16_t *)(q_tail + (size_t)(u_first + u0) * c.head_dim * es);
         p.len0 = prefill_len - n + u_first + u0 + 1;
         p.insert_slot = (int32_t)((h->n_ins + u0) % C);
-        p.overflow = (uint32_t *)ws.mem + u0;
+        p.overflow = words + u0;
+        p.again = (uint64_t *)(mem + plan.again_at) + u0 * BH;
+        p.rerun = run == AGAIN;
         const int64_t len_max = p.len0 + Uc - 1;
         const int64_t vheads = BH * Uc;
         const PrefillGrid grid = prefill_grid(h->G * Uc, groups, len_max);
@@ -401,7 +414,7 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
             return launch_desc(h, d, kid, args, s);
         };
         retopk_status st;
-        if (dense) {
+        if (run == ROWS) {
             p.scores = rows;
             p.score_stride = stride;
             if ((st = launch(PF_DENSE, KID_PF_SCORE)) != RETOPK_OK) return st;
@@ -411,6 +424,11 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
         p.maxima = (float *)mem;
         p.cnt = (uint32_t *)(mem + vheads * cap * 8);
         p.thr = (float *)(p.cnt + vheads);
+        if (run == AGAIN) {
+            if ((st = launch(PF_RAISE, KID_FILTER)) != RETOPK_OK) return st;
+            if ((st = launch(PF_RECOLLECT, KID_PF_SCORE)) != RETOPK_OK) return st;
+            return launch(PF_SELECT_LIST, KID_FINAL);
+        }
         // Key sample of the bound: one tile in F, so that about F K = cap / 4 entries
         // pass it, in groups of 2^lt tiles, so that there are 4 K to 8 K maxima.
         const int64_t tiles = p.len0 / 16;
@@ -436,44 +454,42 @@ retopk_status prefill_batched(retopk_handle h, const char *q_tail, int32_t n, in
     };
     retopk_status st = RETOPK_OK;
     uint32_t over[kMaxCache];            // n_eff <= C (no allocation that could throw)
-    int64_t listed = n_eff;              // first position run with lists: prefixes only grow
-    for (int64_t u0 = 0; u0 < n_eff && st == RETOPK_OK;) {
-        const int64_t Uc = n_eff - u0 < U ? n_eff - u0 : U;
-        const bool dense = !plan.lists || prefill_len - n + u_first + u0 + 1 < cap;
-        if (!dense && listed == n_eff) listed = u0;
-        // (the rows of a launch of short prefixes: fewer than cap + C <= 2 cap of them)
-        st = sequence(u0, Uc, dense, (float *)mem, plan.row_bytes / 4);
-        u0 += Uc;
-    }
-    if (listed < n_eff && st == RETOPK_OK &&
-        hipMemcpyAsync(over, ws.mem, (size_t)n_eff * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
-        st = fail(h);
-    // the call returns once the stream has finished its work
-    if (hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
-    ws.idle = st == RETOPK_OK;
-    // The overflowed positions again, with score rows: as many at a time as fit, or
-    // one in the handle's own score rows.
-    const int64_t fit = (int64_t)(room / ((size_t)BH * (size_t)plan.rows16 * 4));
-    float *const rows = fit > 0 ? (float *)mem : h->w.scores;
-    const int64_t stride = fit > 0 ? plan.rows16 : base_args(h).row_stride;
-    bool again = false;
-    for (int64_t u0 = listed; u0 < n_eff && st == RETOPK_OK;) {
-        if (!over[u0]) {
-            ++u0;
-            continue;
-        }
-        int64_t most = fit > 0 ? fit : 1;
-        if (most > n_eff - u0) most = n_eff - u0;
-        int64_t Uc = 1;
-        for (int64_t i = 1; i < most; ++i)
-            if (over[u0 + i]) Uc = i + 1;
-        st = sequence(u0, Uc, true, rows, stride);
-        again = true;
-        u0 += Uc;
-    }
-    if (again) {
+    // Waits for the stream, the overflow words on the host when lists were used.
+    auto finish = [&]() {
+        if (plan.lists && st == RETOPK_OK &&
+            hipMemcpyAsync(over, words, (size_t)n_eff * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
+            st = fail(h);
         if (hipStreamSynchronize(s) != hipSuccess && st == RETOPK_OK) st = fail(h);
         ws.idle = st == RETOPK_OK;
+    };
+    // The positions with an overflowed list again, up to `most` at a time.
+    auto repeat = [&](Run run, int64_t most) {
+        bool any = false;
+        for (int64_t u0 = 0; u0 < n_eff && st == RETOPK_OK; ++u0) {
+            if (!over[u0]) continue;
+            int64_t Uc = 1;
+            for (int64_t i = 1; i < most && u0 + i < n_eff; ++i)
+                if (over[u0 + i]) Uc = i + 1;
+            st = sequence(u0, Uc, run);
+            any = true;
+            u0 += Uc - 1;
+        }
+        if (any) finish();
+        return any;
+    };
+    for (int64_t u0 = 0; u0 < n_eff && st == RETOPK_OK; u0 += U)
+        st = sequence(u0, n_eff - u0 < U ? n_eff - u0 : U, plan.lists ? LISTS : ROWS);
+    finish();
+    if (plan.lists && st == RETOPK_OK) {
+        bool left = true;
+        for (int i = 0; i < kPfReruns && left && st == RETOPK_OK; ++i) left = repeat(AGAIN, U);
+        // with score rows: as many positions at a time as fit, or one in the handle's own
+        const int64_t fit = plan.again_at / (BH * plan.rows16 * 4);
+        if (fit == 0) {
+            rows = h->w.scores;
+            stride = base_args(h).row_stride;
+        }
+        if (left && st == RETOPK_OK) repeat(ROWS, fit > 0 ? fit : 1);
     }
     h->n_ins += n_eff;
     return st;

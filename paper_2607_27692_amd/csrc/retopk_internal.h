@@ -154,6 +154,9 @@ struct PfArgs {
     uint32_t *cnt;             // [U * BH] entries appended (past cap: overflowed)
     float *thr;                // [U * BH] lower bound of the K-th largest raw score
     uint32_t *overflow;        // [U] set: some head of the position overflowed its list
+    uint64_t *again;           // [U * BH] of an overflowed list: the K-th largest rank it
+                               // holds, a lower bound of the head's; else 0
+    int rerun;                 // lists of the heads with such a bound only
     // the cache
     float *qbar;
     int32_t *supp;
@@ -161,7 +164,7 @@ struct PfArgs {
     int32_t insert_slot;       // slot of position 0
 };
 enum : int { PF_BOUND = 0, PF_COLLECT = 1, PF_DENSE = 2, PF_THRESHOLD = 3, PF_SELECT_LIST = 4,
-             PF_SELECT_DENSE = 5 };
+             PF_SELECT_DENSE = 5, PF_RAISE = 6, PF_RECOLLECT = 7 };
 
 // One kernel of a step, ready to launch (hipLaunchKernel): the kernel takes
 // (StepArgs, Ws) when nargs == 2 and (StepArgs, Ws, Geometry) when nargs == 3, or

@@ -135,8 +135,9 @@ struct PrefillPlan {
     int64_t rows16;            // rows of a score row: the prompt in whole tiles
     int64_t row_bytes;         // memory of a virtual head's list or score row
     int64_t positions;         // positions a launch takes
-    bool lists;                // launches keep lists, else score rows
-    int64_t head_bytes, bytes; // words per position; the whole workspace
+    bool lists;                // launches keep lists (prompts of 2 cap rows on), else score rows
+    int64_t again_at, over_at; // offsets of the overflowed lists' bounds and of the words
+    int64_t bytes;             // the whole workspace
 };
 
 // n positions of `heads` query heads, G to a KV group, of a prompt of prefill_len rows.
@@ -149,7 +150,7 @@ inline PrefillPlan prefill_plan(int64_t heads, int G, int64_t K, int64_t n, int6
     // A list of cap ranks, which also holds its group maxima (at most 8 K floats), or a
     // score row of up to 2 cap rows; beside it the count and the bound.
     p.row_bytes = p.rows16 * 4 < p.cap * 8 ? p.rows16 * 4 : p.cap * 8;
-    p.lists = p.row_bytes == p.cap * 8 && prefill_len > p.cap;
+    p.lists = p.rows16 >= 2 * p.cap;
     const int64_t per_u = heads * (p.row_bytes + 8);
     int64_t U = kPfWorkspaceBytes / per_u;
     // whole 128-query tiles where the budget allows
@@ -162,9 +163,11 @@ inline PrefillPlan prefill_plan(int64_t heads, int G, int64_t K, int64_t n, int6
     const int64_t unit = kPfWaveCols / gcd;
     if (U >= unit) U -= U % unit;
     p.positions = U < 1 ? 1 : (U > n ? n : U);
-    // overflow words of every position, then the virtual heads' memory
-    p.head_bytes = ceil_div(n * 4, 256) * 256;
-    p.bytes = p.head_bytes + per_u * p.positions;
+    // the virtual heads' memory, then the bounds that every position's lists leave and
+    // its overflow word
+    p.again_at = ceil_div(per_u * p.positions, 256) * 256;
+    p.over_at = p.again_at + n * heads * 8;
+    p.bytes = p.over_at + n * 4;
     return p;
 }
 

@@ -17,13 +17,21 @@
 //   k_pf_select         the exact Top-K of each list, in index order (through an
 //                       index bitmap), and the cache entry.
 // For exchangeable keys the bound leaves about F * K entries (F: one key tile in
-// F is sampled).  A list that overflows (thousands of equal scores, or keys whose
-// scores cluster far more than a tile group) is reported per position, and the
-// host runs those positions again with k_pf_scan<DENSE>, which stores every score
-// row, and the same k_pf_select; so do launches whose shortest prefix is no
-// longer than a list.
+// F is sampled).  Keys whose high scores lie in long runs leave more, up to the
+// list's capacity and past it, and so do thousands of equal scores.  The K-th
+// largest entry of a full list, whichever entries it holds, bounds the head's K-th
+// from below again, and more tightly: k_pf_select stores it, k_pf_raise makes it
+// the head's bound, and k_pf_scan<RECOLLECT> collects the entries at or above it, by
+// rank (score, then index), so that ties are cut too (512 positions of 32/8 heads at
+// 128K, K = 512: keys with neighbour correlation 0.999 2.2 ms, 18.3 with score rows;
+// half the keys one row 3.1 ms, 29.0; all of them 14.0 ms, 23.3).  Positions with a list
+// that still overflows after a few such runs are scored with k_pf_scan<DENSE>, which
+// stores every score row, and the same k_pf_select; so are prompts of fewer than two
+// lists' rows.
 #include "retopk_internal.h"
 #include "retopk_device.h"
+
+#include <cfloat>
 
 namespace retopk {
 
@@ -36,6 +44,13 @@ constexpr int kPfSelThreads = 256;    // k_pf_bound and k_pf_select blocks
 constexpr int kPfBins = 1024;         // value-linear bins
 constexpr int kPfTie = 64;            // entries of the last bin ranked by lane
 constexpr int kPfSegBits = 131072;    // indices per bitmap pass
+
+// A raw score below t by more than the rounding that can make two raw scores one scaled
+// score, and finite where t is +inf.
+__device__ __forceinline__ float raw_bound(float t)
+{
+    return t < FLT_MAX ? t - fabsf(t) * 1.0e-6f - 1.0e-37f : FLT_MAX;
+}
 
 // The larger of two finite scores, without the quieting that fmaxf does first.
 __device__ __forceinline__ float fmax_nan(float x, float y) { return __builtin_elementwise_maximum(x, y); }
@@ -64,13 +79,14 @@ template <int D, int MODE>
 __global__ __launch_bounds__(kPfThreads, 2) void k_pf_scan(PfArgs a)
 {
     constexpr int KS = D / 32, CT = kPfWaveCols / 16;
+    constexpr bool LIST = MODE == PF_COLLECT || MODE == PF_RECOLLECT;
     __shared__ int s_vh[kPfWaves * kPfWaveCols];    // virtual head of a column, -1: padding
     __shared__ u32x4_t s_key[2][kPfWaves][KS][64];
-    constexpr int CW = MODE == PF_COLLECT ? kPfWaves : 1, CQ = MODE == PF_COLLECT ? kPfQueue : 1;
+    constexpr int CW = LIST ? kPfWaves : 1, CQ = LIST ? kPfQueue : 1;
     __shared__ f32x4_t s_qv[CW][CQ];                 // queued quads: raw scores of 4 keys
     __shared__ uint32_t s_qi[CW][CQ];                // their column << 24 | first key
     __shared__ uint32_t s_cur[CW][kPfWaveCols];
-    __shared__ float s_thr[MODE == PF_COLLECT ? kPfWaves * kPfWaveCols : 1];
+    __shared__ float s_thr[LIST ? kPfWaves * kPfWaveCols : 1];
     __shared__ float s_mx[MODE == PF_BOUND ? kPfWaves : 1][MODE == PF_BOUND ? kPfMaxima : 1][CT][64];
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, kq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -154,11 +170,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void k_pf_scan(PfArgs a)
         const u32x4_t *qr = (const u32x4_t *)(a.q + (int64_t)bh * a.q_head_stride + (int64_t)u * D);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qb[ct][ks] = __builtin_bit_cast(bf16x8_t, qr[ks * 4 + kq]);
-        thr[ct] = MODE == PF_COLLECT && vh >= 0 ? a.thr[vh] : INFINITY;
-        if (MODE == PF_COLLECT) s_thr[cbase + ct * 16 + col] = thr[ct];   // same value from each wave and kq
+        thr[ct] = LIST && vh >= 0 ? a.thr[vh] : INFINITY;
+        if (LIST) s_thr[cbase + ct * 16 + col] = thr[ct];   // same value from each wave and kq
     }
 
-    // --- COLLECT: the wave's queue of entries and its append to the lists
+    // --- COLLECT, RECOLLECT: the wave's queue of entries and its append to the lists
     uint32_t qn = 0u;
     auto flush = [&]() {
         uint32_t *cur = s_cur[wave];
@@ -169,6 +185,16 @@ __global__ __launch_bounds__(kPfThreads, 2) void k_pf_scan(PfArgs a)
         auto passing = [&](uint32_t i, uint32_t &c, f32x4_t &v) {
             c = s_qi[wave][i] >> 24;
             v = s_qv[wave][i];
+            if constexpr (MODE == PF_RECOLLECT) {
+                const int vh = s_vh[cbase + c];
+                const uint64_t least = vh >= 0 ? a.again[vh] : 0ull;
+                const uint32_t row = s_qi[wave][i] & 0xFFFFFFu;
+                uint32_t m = 0u;
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (least != 0ull && rank_of(v[x] * a.inv_sqrt_d, row + x) >= least) m |= 1u << x;
+                return m;
+            }
             const float t = s_thr[cbase + c];
             return (v[0] >= t ? 1u : 0u) | (v[1] >= t ? 2u : 0u) | (v[2] >= t ? 4u : 0u) | (v[3] >= t ? 8u : 0u);
         };
@@ -277,7 +303,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void k_pf_scan(PfArgs a)
             }
         } else {
             const int64_t row = row_of(wk, it);
-            if constexpr (MODE == PF_COLLECT) {
+            if constexpr (LIST) {
                 // past the shortest prefix of the launch a column's own limit counts
                 if (row + 16 > a.len0) {
 #pragma unroll
@@ -320,12 +346,12 @@ __global__ __launch_bounds__(kPfThreads, 2) void k_pf_scan(PfArgs a)
         for (int ks = 0; ks < KS; ++ks) s_key[(st + 1) & 1][wave][ks][lane] = ny[ks];
         // The waves' queues fill alike: emptied here they hold up the barrier together,
         // and no key load in flight has to wait for the appends.
-        if constexpr (MODE == PF_COLLECT) {
+        if constexpr (LIST) {
             if (qn >= (uint32_t)kPfQueue * 3 / 8) flush();
         }
         __syncthreads();
     }
-    if constexpr (MODE == PF_COLLECT) {
+    if constexpr (LIST) {
         if (qn != 0u) flush();
     }
 }
@@ -333,8 +359,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void k_pf_scan(PfArgs a)
 // k_pf_bound: per virtual head, a lower bound of its K-th largest raw score (q.k
 // before the 1/sqrt d factor): the smallest of the maxima in the bins at or above
 // the one that holds the K-th largest of them (value-linear bins, so at least K
-// maxima are at or above it), less the rounding that can make two raw scores one
-// scaled score.  Clears the head's list.
+// maxima are at or above it), less the rounding.  Clears the head's list.
 template <int VPT>
 __global__ __launch_bounds__(kPfSelThreads) void k_pf_bound(PfArgs a)
 {
@@ -344,7 +369,7 @@ __global__ __launch_bounds__(kPfSelThreads) void k_pf_bound(PfArgs a)
     const int tid = threadIdx.x, vh = blockIdx.x, M = 4 * a.n_groups;
     const float *mx = a.maxima + (int64_t)vh * 2 * a.cap;
     for (int i = tid; i < kPfBins; i += NT) s_hist[i] = 0u;
-    float x[VPT];              // loads in flight together; padded with the smallest
+    float x[VPT];              // loads in flight together; padded with the first
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
     for (int i = 0; i < VPT; ++i) x[i] = mx[tid + i * NT < M ? tid + i * NT : 0];
@@ -353,16 +378,24 @@ __global__ __launch_bounds__(kPfSelThreads) void k_pf_bound(PfArgs a)
         lo = fminf(lo, x[i]);
         hi = fmaxf(hi, x[i]);
     }
-    lo = block_reduce<NT>(lo, s_red, [](float x, float y) { return fminf(x, y); });
+    auto smaller = [](float x, float y) { return fminf(x, y); };
+    lo = block_reduce<NT>(lo, s_red, smaller);
     hi = block_reduce<NT>(hi, s_red, [](float x, float y) { return fmaxf(x, y); });
-    const float range = hi - lo;
     float t = lo;
+    if (lo == -INFINITY) {
+        // masked rows (scores of -inf) share the lowest bin and do not stretch the others
+        lo = INFINITY;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) lo = fminf(lo, x[i] > -INFINITY ? x[i] : INFINITY);
+        lo = block_reduce<NT>(lo, s_red, smaller);
+    }
+    const float range = hi - lo;
     if (range > 0.0f && range < 3.0e38f) {      // block-uniform
         const float scale = (float)(kPfBins - 1) / range;
         int bin[VPT];
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
-            bin[i] = min(max((int)((x[i] - lo) * scale), 0), kPfBins - 1);
+            bin[i] = min((int)fmaxf((x[i] - lo) * scale, 0.0f), kPfBins - 1);
             if (tid + i * NT < M) atomicAdd(&s_hist[bin[i]], 1u);
         }
         __syncthreads();
@@ -372,13 +405,27 @@ __global__ __launch_bounds__(kPfSelThreads) void k_pf_bound(PfArgs a)
 #pragma unroll
         for (int i = 0; i < VPT; ++i)
             if (bin[i] >= (int)bstar) t = fminf(t, x[i]);
-        t = block_reduce<NT>(t, s_red, [](float x, float y) { return fminf(x, y); });
+        t = block_reduce<NT>(t, s_red, smaller);
     }
     if (tid == 0) {
-        a.thr[vh] = t - fabsf(t) * 1.0e-6f - 1.0e-37f;
+        a.thr[vh] = raw_bound(t);
         a.cnt[vh] = 0u;
         a.overflow[vh / (a.B * a.Hq)] = 0u;
     }
+}
+
+// k_pf_raise: prepares k_pf_scan<RECOLLECT>, one thread per virtual head: the raw score
+// that the stored rank implies as the bound of an overflowed list, which is cleared; no
+// raw score for the others.
+__global__ __launch_bounds__(kPfSelThreads) void k_pf_raise(PfArgs a)
+{
+    const int vh = blockIdx.x * kPfSelThreads + threadIdx.x, BH = a.B * a.Hq;
+    if (vh >= BH * a.U) return;
+    const uint64_t least = a.again[vh];
+    const float s = key_score(rank_key(least));
+    a.thr[vh] = least == 0ull ? INFINITY : raw_bound(s > -FLT_MAX ? s / a.inv_sqrt_d : -INFINITY);
+    a.cnt[vh] = 0u;
+    if (vh % BH == 0) a.overflow[vh / BH] = 0u;
 }
 
 // k_pf_select: one block per virtual head: the Top-K (Eq. 1) of its entries -- its
@@ -387,7 +434,8 @@ __global__ __launch_bounds__(kPfSelThreads) void k_pf_bound(PfArgs a)
 // entry in one bin, ranked exactly when it holds at most kPfTie entries; heavier
 // ties take a radix select on the 64-bit ranks.  The selected indices pass through
 // a bitmap, which orders them without a sort (a bitmap pass covers kPfSegBits
-// rows).  A virtual head's list is about 1100 entries at K = 512, held in
+// rows).  Of a list that overflowed (cap >= 8 K entries) only the K-th largest entry is
+// found, the bound of its next run.  A virtual head's list is about 1100 entries at K = 512, held in
 // registers; longer ones are read three times, after the first from the caches.
 // 22 KB of LDS a block keep seven blocks on a CU.
 template <int D, bool DENSE>
@@ -414,11 +462,9 @@ __global__ __launch_bounds__(kPfSelThreads) void k_pf_select(PfArgs a)
     const uint64_t *list = DENSE ? nullptr : a.list + (int64_t)vh * a.cap;
     const uint32_t n_list = DENSE ? 0u : a.cnt[vh];
     const uint16_t *q = a.q + (int64_t)bh * a.q_head_stride + (int64_t)u * D;
-    if (!DENSE && n_list > (uint32_t)a.cap) {        // block-uniform
-        if (tid == 0) a.overflow[u] = 1u;
-        return;
-    }
-    const int n = DENSE ? (int)clen : (int)n_list;
+    if (!DENSE && a.rerun && a.again[vh] == 0ull) return;      // selected before (block-uniform)
+    const bool over = !DENSE && n_list > (uint32_t)a.cap;      // holds cap of its entries
+    const int n = DENSE ? (int)clen : over ? a.cap : (int)n_list;
     auto get = [&](int j) -> uint64_t {
         if constexpr (DENSE) return rank_of(row[j], (uint32_t)j);
         else return list[j];
@@ -531,6 +577,13 @@ __global__ __launch_bounds__(kPfSelThreads) void k_pf_select(PfArgs a)
         }
     }
 
+    if constexpr (!DENSE) {
+        if (tid == 0) a.again[vh] = over ? thr : 0ull;
+        if (over) {                                            // block-uniform
+            if (tid == 0) a.overflow[u] = 1u;
+            return;
+        }
+    }
     const int64_t slot = (int64_t)bh * a.M + (a.insert_slot + u) % a.M;
     int32_t *dst = a.supp + slot * K;
     const int kn = n < K ? n : K;
@@ -585,6 +638,14 @@ void describe_prefill(int which, const PfArgs &a, KernelDesc *k)
     case PF_COLLECT:
         *k = KernelDesc{d64 ? (const void *)&k_pf_scan<64, PF_COLLECT> : (const void *)&k_pf_scan<128, PF_COLLECT>,
                         dim3(scan_blocks), dim3(kPfThreads), 0u, 1};
+        return;
+    case PF_RECOLLECT:
+        *k = KernelDesc{d64 ? (const void *)&k_pf_scan<64, PF_RECOLLECT> : (const void *)&k_pf_scan<128, PF_RECOLLECT>,
+                        dim3(scan_blocks), dim3(kPfThreads), 0u, 1};
+        return;
+    case PF_RAISE:
+        *k = KernelDesc{(const void *)&k_pf_raise, dim3((vheads + kPfSelThreads - 1) / kPfSelThreads),
+                        dim3(kPfSelThreads), 0u, 1};
         return;
     case PF_DENSE:
         *k = KernelDesc{d64 ? (const void *)&k_pf_scan<64, PF_DENSE> : (const void *)&k_pf_scan<128, PF_DENSE>,

@@ -13,7 +13,7 @@ import pytest
 from gpu_harness import Tally, check_selection, handle_of, params_of, to_dev, torch_cuda
 from oracle import oracle as O
 from paper_2607_27692_amd import retopk as R
-from paper_2607_27692_amd.inputs import WORKLOADS, make_inputs
+from paper_2607_27692_amd.inputs import WORKLOADS, bf16_bits_to_f32, make_inputs, to_bf16_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -210,6 +210,72 @@ def test_prefill_batched_bounds_and_lists(label, change, equal):
     _compare_states(p, gst, orc.get_state(), list(range(p.heads)), inp.q_tail, kf, w.prompt_len,
                     tally)
     print(tally, flush=True)
+
+
+def _launches(p, dtype, q_tail_raw, k_raw, prefill_len):
+    """State after a prefill, and its launches: (score products, bounds, selections)."""
+    torch = torch_cuda()
+    with handle_of(p, dtype) as h:
+        h.profile(True)
+        q, k = to_dev(q_tail_raw), to_dev(k_raw)
+        h.prefill_init(q, q_tail_raw.shape[-2], k, k, prefill_len)
+        torch.cuda.synchronize()
+        prof = h.profile_read()
+        return h.get_state(), tuple(prof[x][0] for x in ("prefill_score", "retopk_filter", "retopk_final"))
+
+
+def _segments(k, rng, lead):
+    """Rows 2000 .. 7999 in 6 segments of one score level each, far above the other rows
+    for a query along `lead`: more rows than a list holds reach the bound that a sample
+    of the keys gives."""
+    for j, level in enumerate(rng.permutation(6)):
+        k[:, :, 2000 + 1000 * j:3000 + 1000 * j] = (6.0 + 0.5 * level) * lead
+
+
+def _masked(k, rng, lead):
+    """The first 5000 rows masked with nearly the lowest bf16 value."""
+    k[:, :, :5000] = -3.0e38
+
+
+def _equal_run(k, rng, lead):
+    """6000 equal rows above all others: ties far past a list's capacity."""
+    k[:, :, 1000:7000] = 8.0 * lead
+
+
+@pytest.mark.parametrize("keys, reruns", [(_segments, (1, 1)), (_masked, (0, 0)), (_equal_run, (1, 3))],
+                         ids=["segments", "masked", "equal_run"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_prefill_overflowing_lists(keys, reruns, d):
+    """Lists that overflow are collected again above the K-th largest entry they hold,
+    and no score row is stored; masked rows do not make a list overflow."""
+    print(f"batched prefill {keys.__name__} d={d}", flush=True)
+    rng = np.random.default_rng(d)
+    L, K, C, Hq, Hkv = 17000, 512, 6, 4, 2
+    lead = (np.abs(rng.standard_normal(d)) + 0.5).astype(np.float32)
+    q = (0.2 * rng.standard_normal((1, Hq, C, d)) + lead).clip(0.05).astype(np.float32)
+    k = rng.standard_normal((1, Hkv, L, d)).astype(np.float32)
+    keys(k, rng, lead)
+    q_raw, k_raw = to_bf16_bits(q), to_bf16_bits(k)
+    q, k = bf16_bits_to_f32(q_raw), bf16_bits_to_f32(k_raw)
+    p = O.Params(1, Hq, Hkv, d, L, K, C, 1, 0, 0.5, 0)
+    gst, (scores, bounds, selects) = _launches(p, "bf16", q_raw, k_raw, L)
+    tally = Tally()
+    for bh in range(Hq):
+        for u in range(C):
+            length = L - C + u + 1
+            # masked rows overflow fp32, which the fp64 order of the other rows never reaches
+            universe = np.arange(5000 if keys is _masked else 0, length, dtype=np.int32)
+            s = O.scores(q[0, bh, u], k[0, bh // (Hq // Hkv)], universe)
+            want = np.sort(universe[np.lexsort((universe, -s))[:K]])
+            got = gst["supp"][bh, u]
+            assert gst["cnt"][bh, u] == K
+            if np.array_equal(got, want):
+                tally.exact += 1
+            else:
+                check_selection(got, want, universe, s, f"h={bh} position {u}", tally)
+    print(tally, f"launches {scores} {bounds} {selects}", flush=True)
+    assert scores == 1 + bounds and selects == bounds, "some positions stored score rows"
+    assert reruns[0] <= bounds - 1 <= reruns[1]
 
 
 def _workspace_case(seed):

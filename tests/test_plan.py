@@ -21,8 +21,8 @@ long t_f32_chunks(long g, long max_len) { return dense_f32_chunks(g, max_len); }
 void t_prefill_plan(long heads, int G, long K, long n, long len, long *out)
 {
     const PrefillPlan p = prefill_plan(heads, G, K, n, len);
-    const long v[] = {p.cap, p.rows16, p.row_bytes, p.positions, p.lists, p.head_bytes, p.bytes};
-    for (int i = 0; i < 7; ++i) out[i] = v[i];
+    const long v[] = {p.cap, p.rows16, p.row_bytes, p.positions, p.lists, p.again_at, p.over_at, p.bytes};
+    for (int i = 0; i < 8; ++i) out[i] = v[i];
 }
 void t_prefill_grid(long cols, long groups, long rows, long *out)
 {
@@ -58,7 +58,8 @@ def plan(tmp_path_factory):
 
     def prefill_plan(*args):
         p.t_prefill_plan(*args, out)
-        return dict(zip(("cap", "rows16", "row_bytes", "positions", "lists", "head_bytes", "bytes"), out))
+        return dict(zip(("cap", "rows16", "row_bytes", "positions", "lists", "again_at", "over_at",
+                         "bytes"), out))
 
     def prefill_grid(*args):
         p.t_prefill_grid(*args, out)
@@ -183,8 +184,10 @@ def test_prefill_plan_limits(plan):
                         continue
                     p = plan.prefill_plan(heads, G, K, n, length)
                     assert 1 <= p["positions"] <= n
-                    assert p["bytes"] - p["head_bytes"] == heads * (p["row_bytes"] + 8) * p["positions"]
-                    assert p["bytes"] <= max(258 << 20, (heads * (p["row_bytes"] + 8)) + (1 << 20))
+                    assert p["again_at"] >= heads * (p["row_bytes"] + 8) * p["positions"]
+                    assert p["again_at"] % 8 == 0 and p["over_at"] % 4 == 0
+                    assert p["over_at"] >= p["again_at"] + 8 * n * heads and p["bytes"] >= p["over_at"] + 4 * n
+                    assert p["again_at"] <= max(257 << 20, heads * (p["row_bytes"] + 8) + 256)
                     if p["lists"]:
                         assert p["row_bytes"] == 8 * p["cap"] and p["cap"] >= 8 * K
                     else:
