@@ -3,8 +3,8 @@ with the last C prompt queries, each inserted with its Exact Top-K support over
 its causal prefix) against the oracle's query-by-query prefill.
 
 bf16 handles score U prompt positions x all heads per launch on the matrix
-cores and select them with the same filter and final kernels as the decode
-step; the cache state they leave (normalised queries, supports, counts,
+cores and select them from lists of the entries above a bound, or for short
+prompts from stored score rows; the cache state they leave (normalised queries, supports, counts,
 insertion count) must equal the oracle's, supports up to near-ties at the K
 boundary (same rule as the decode parity tests)."""
 import numpy as np
@@ -148,10 +148,11 @@ def test_prefill_batched_shapes(label, change, extra):
     print(tally, flush=True)
 
 
-def test_prefill_batched_equal_keys():
+@pytest.mark.parametrize("prompt_len", [6000, 9000])      # by score rows, by lists
+def test_prefill_batched_equal_keys(prompt_len):
     """Identical key rows: every score of a query ties, so each support is the K
     lowest positions of its prefix (Top-K ties broken by index)."""
-    w = WORKLOADS["16k"].with_(n_q_heads=8, n_kv_heads=2, prompt_len=6000, k=300,
+    w = WORKLOADS["16k"].with_(n_q_heads=8, n_kv_heads=2, prompt_len=prompt_len, k=300,
                                cache_cap=16, n_centers=8)
     print("batched prefill equal keys", flush=True)
     inp = make_inputs(w)
@@ -167,31 +168,53 @@ def test_prefill_batched_equal_keys():
     assert np.array_equal(gst["cnt"], ost["cnt"])
 
 
+def _launches(p, dtype, q_tail_raw, k_raw, prefill_len):
+    """State after a prefill, and its launches: (score products, bounds, selections)."""
+    torch = torch_cuda()
+    with handle_of(p, dtype) as h:
+        h.profile(True)
+        q, k = to_dev(q_tail_raw), to_dev(k_raw)
+        h.prefill_init(q, q_tail_raw.shape[-2], k, k, prefill_len)
+        torch.cuda.synchronize()
+        prof = h.profile_read()
+        return h.get_state(), tuple(prof[x][0] for x in ("prefill_score", "retopk_filter", "retopk_final"))
+
+
 BOUND_SHAPES = [
-    # label, workload changes, what the key rows are replaced with
-    # launches on both sides of the list capacity (4096): score rows, then lists
-    ("around_capacity", dict(n_q_heads=8, n_kv_heads=2, prompt_len=4103, k=64, cache_cap=20,
-                             n_centers=16), None),
-    # K = 1 and K = 2048 (list capacity 16384, group maxima of single tiles)
-    ("k1", dict(n_q_heads=4, n_kv_heads=1, prompt_len=7001, k=1, cache_cap=9, n_centers=16), None),
-    ("k2048_d64", dict(n_q_heads=2, n_kv_heads=2, head_dim=64, prompt_len=17001, k=2048,
-                       cache_cap=6, n_centers=16), None),
-    # 140 virtual queries a group: two waves side by side, padded columns; a prefix past
-    # one bitmap pass is covered by the 128K cases' last position
-    ("two_query_tiles", dict(n_q_heads=7, n_kv_heads=1, prompt_len=6003, k=40, cache_cap=20,
-                             n_centers=16), None),
+    # label, workload changes, equal key rows, whether lists are kept (prompts of 2 cap
+    # rows on, cap = max(8 K, 4096))
+    # the last prompt of score rows and the first of lists, of more positions than
+    # fit between one and two lists' rows: prefixes from 4081 and 4082 rows on
+    ("below_2cap", dict(n_q_heads=2, n_kv_heads=1, head_dim=64, prompt_len=8176, k=64,
+                        cache_cap=4096, n_centers=16), None, False),
+    ("from_2cap", dict(n_q_heads=2, n_kv_heads=1, head_dim=64, prompt_len=8177, k=512,
+                       cache_cap=4096, n_centers=16), None, True),
+    # K = 1, and K = 2048 (list capacity 16384, group maxima of single tiles)
+    ("k1", dict(n_q_heads=4, n_kv_heads=1, prompt_len=9001, k=1, cache_cap=9, n_centers=16), None, True),
+    ("k2048_d64", dict(n_q_heads=2, n_kv_heads=2, head_dim=64, prompt_len=33001, k=2048,
+                       cache_cap=6, n_centers=16), None, True),
+    # more than 4096 group maxima
+    ("maxima_5000", dict(n_q_heads=4, n_kv_heads=2, prompt_len=40000, k=1024, cache_cap=5,
+                         n_centers=16), None, True),
+    # 140 virtual queries a group: two waves side by side, padded columns
+    ("two_query_tiles", dict(n_q_heads=7, n_kv_heads=1, prompt_len=8203, k=40, cache_cap=20,
+                             n_centers=16), None, True),
+    # prefixes past one bitmap pass (131072 rows)
+    ("two_bitmap_passes", dict(n_q_heads=2, n_kv_heads=1, head_dim=64, prompt_len=140003, k=64,
+                               cache_cap=3, n_centers=64), None, True),
     # for about half of the queries the best keys are one run of equal rows longer than
-    # a list: those lists overflow and the positions run again with score rows
+    # a list
     ("overflow", dict(n_q_heads=4, n_kv_heads=2, prompt_len=9000, k=50, cache_cap=5,
-                      n_centers=8), (1000, 7000)),
+                      n_centers=8), (1000, 7000), True),
 ]
 
 
-@pytest.mark.parametrize("label,change,equal", BOUND_SHAPES, ids=[s[0] for s in BOUND_SHAPES])
-def test_prefill_batched_bounds_and_lists(label, change, equal):
-    """The bounded selection of the batched prefill where it can go wrong: list
-    capacity, the smallest and largest K, padded query columns, lists that
-    overflow.  Supports exact up to near-ties, as in the other cases."""
+@pytest.mark.parametrize("label,change,equal,lists", BOUND_SHAPES, ids=[s[0] for s in BOUND_SHAPES])
+def test_prefill_batched_bounds_and_lists(label, change, equal, lists):
+    """The bounded selection of the batched prefill where it can go wrong: the prompts
+    it begins with, the smallest and largest K, padded query columns, many maxima, several
+    bitmap passes, lists that overflow.  Supports exact up to near-ties, as in the other
+    cases, and the launches tell which path ran."""
     w = WORKLOADS["16k"].with_(**change)
     print(f"batched prefill {label}", flush=True)
     inp = make_inputs(w)
@@ -205,23 +228,17 @@ def test_prefill_batched_bounds_and_lists(label, change, equal):
     p = params_of(w)
     orc = O.Oracle(p)
     orc.prefill_init(inp.q_tail, kf, inp.v, w.prompt_len)
-    gst = _gpu_prefill(p, w.dtype, inp.q_tail_raw, k_raw, inp.v_raw, w.prompt_len)
+    gst, (scores, bounds, selects) = _launches(p, w.dtype, inp.q_tail_raw, k_raw, w.prompt_len)
     tally = Tally()
     _compare_states(p, gst, orc.get_state(), list(range(p.heads)), inp.q_tail, kf, w.prompt_len,
                     tally)
-    print(tally, flush=True)
-
-
-def _launches(p, dtype, q_tail_raw, k_raw, prefill_len):
-    """State after a prefill, and its launches: (score products, bounds, selections)."""
-    torch = torch_cuda()
-    with handle_of(p, dtype) as h:
-        h.profile(True)
-        q, k = to_dev(q_tail_raw), to_dev(k_raw)
-        h.prefill_init(q, q_tail_raw.shape[-2], k, k, prefill_len)
-        torch.cuda.synchronize()
-        prof = h.profile_read()
-        return h.get_state(), tuple(prof[x][0] for x in ("prefill_score", "retopk_filter", "retopk_final"))
+    print(tally, f"launches {scores} {bounds} {selects}", flush=True)
+    if not lists:
+        assert bounds == 0 and scores == selects
+    elif equal is None:
+        assert scores == 2 * bounds and selects == bounds       # bound and list per launch
+    else:
+        assert scores == 1 + bounds and selects == bounds > 1   # lists again, no score rows
 
 
 def _segments(k, rng, lead):
