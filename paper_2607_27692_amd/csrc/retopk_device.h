@@ -90,9 +90,6 @@ __device__ __forceinline__ double quad_sum(double x)
     return x;
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave: Hillis-Steele inside each row
-// of 16 lanes (DPP row shifts, lanes shifted in from outside the row read 0), then
-// the row totals carried across rows with the row broadcasts of lanes 15 and 31.
 // Reductions over a wave: DPP inside each row of 16 lanes (quad swaps, half-row
 // and row mirrors), then the four row results read as scalars.  Every lane gets
 // the result.
@@ -186,6 +183,9 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave: Hillis-Steele inside each row
+// of 16 lanes (DPP row shifts, lanes shifted in from outside the row read 0), then
+// the row totals carried across rows with the row broadcasts of lanes 15 and 31.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
 {
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr:1
@@ -242,7 +242,6 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *red, u
 template <typename T, int D> struct RowT {
     static constexpr int kBytes = D * (int)sizeof(T);
     static constexpr int kNV = kBytes / 64;
-    static constexpr int kEPV = 16 / (int)sizeof(T);
 };
 
 // Waves per SIMD that k_score is built for: 4 (two 512-thread blocks per CU), or
@@ -255,12 +254,12 @@ template <typename T, int D, int G>
 constexpr int kGroupWaves = (G == 8 && sizeof(T) == 2) ? 4
                             : G == 8 ? (2 * G * RowT<T, D>::kNV > 64 ? 2 : 4)
                                      : ((G + 2) * RowT<T, D>::kNV * 4 > 96 ? 2 : 4);
-// The same for k_dense, whose lanes also hold G value accumulators of kEPV floats
-// (the 8-head build takes its scores in the octet layout, its queries dead by
-// the time the accumulators live).
-template <typename T, int D, int G>
-constexpr int kDenseWaves = G == 8 ? (16 * RowT<T, D>::kNV > 64 ? 2 : 4)
-                                   : (G * (4 * RowT<T, D>::kNV + RowT<T, D>::kEPV) > 96 ? 2 : 4);
+// The same for k_dense (fp32), whose lanes also hold G value accumulators of 4 floats
+// (the 8-head build takes its scores in the octet layout, its queries dead by the time
+// the accumulators live).
+template <int D, int G>
+constexpr int kDenseWaves = G == 8 ? (16 * RowT<float, D>::kNV > 64 ? 2 : 4)
+                                   : (G * 4 * (RowT<float, D>::kNV + 1) > 96 ? 2 : 4);
 
 template <typename T> struct Dot;
 template <> struct Dot<uint16_t> {

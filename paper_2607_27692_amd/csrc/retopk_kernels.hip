@@ -1918,14 +1918,14 @@ __global__ __launch_bounds__(kFinalThreads) void k_final(StepArgs a, Ws w)
 // scores with the scan's row geometry, then per head the chunk's maximum m, the
 // weights exp(s - m), their sum l and the weighted sum o of the value rows.
 // (o, m, l) go to dense_part; k_dense_merge rescales and adds the chunks.
-template <typename T, int D, int G>
-__global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense(StepArgs a, Ws w)
+template <int D, int G>
+__global__ __launch_bounds__(kDenseThreads, (kDenseWaves<D, G>)) void k_dense(StepArgs a, Ws w)
 {
-    using R = RowT<T, D>;
+    using R = RowT<float, D>;
     constexpr int NT = kDenseThreads, NW = NT / 64;
-    constexpr int VL = D * (int)sizeof(T) / 16;     // lanes per value row (16 bytes each)
+    constexpr int VL = D / 4;                        // lanes per value row (16 bytes each)
     constexpr int VR = 64 / VL;                      // value rows per wave instruction
-    constexpr int EPV = 16 / (int)sizeof(T);
+    constexpr int EPV = 4;
     static_assert(VL >= 1 && VL <= 64 && 64 % VL == 0, "value row geometry");
     __shared__ float s_sc[G][kDenseRows];
     __shared__ float s_red[NW][G];
@@ -1938,8 +1938,8 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
     const int bh0 = b * a.Hq + g * a.G;      // heads past a.G pad the group
     const int64_t r0 = (int64_t)c * a.dense_rows;
     const int nrow = (int)(a.len - r0 < a.dense_rows ? a.len - r0 : a.dense_rows);
-    const T *kbase = (const T *)a.k + ((int64_t)b * a.Hkv + g) * a.max_len * D;
-    const T *vbase = (const T *)a.v + ((int64_t)b * a.Hkv + g) * a.max_len * D;
+    const float *kbase = (const float *)a.k + ((int64_t)b * a.Hkv + g) * a.max_len * D;
+    const float *vbase = (const float *)a.v + ((int64_t)b * a.Hkv + g) * a.max_len * D;
 
     if constexpr (G == 8) {
         // scores (Eq. 4) of the chunk's rows in the octet layout of
@@ -1950,7 +1950,7 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             const int hj = j < a.G ? j : 0;
-            const uint4 *qr = (const uint4 *)((const T *)a.q + (int64_t)(bh0 + hj) * a.q_head_stride);
+            const uint4 *qr = (const uint4 *)((const float *)a.q + (int64_t)(bh0 + hj) * a.q_head_stride);
 #pragma unroll
             for (int v = 0; v < NV; ++v) qv[j][v] = qr[v * 8 + o];
         }
@@ -1971,7 +1971,7 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
                 for (int j = 0; j < G; ++j) {
                     float s0 = 0.0f;
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) s0 = Dot<T>::f(kv[u][v], qv[j][v], s0);
+                    for (int v = 0; v < NV; ++v) s0 = Dot<float>::f(kv[u][v], qv[j][v], s0);
                     acc[j] = s0;
                 }
                 const float sc = octet_transpose_sum(acc, o) * a.inv_sqrt_d;
@@ -1983,7 +1983,7 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
 #pragma unroll
     for (int j = 0; j < G; ++j) {
         const int hj = j < a.G ? j : 0;
-        const uint4 *qr = (const uint4 *)((const T *)a.q + (int64_t)(bh0 + hj) * a.q_head_stride);
+        const uint4 *qr = (const uint4 *)((const float *)a.q + (int64_t)(bh0 + hj) * a.q_head_stride);
 #pragma unroll
         for (int v = 0; v < R::kNV; ++v) qv[j][v] = qr[v * 4 + p];
     }
@@ -2005,7 +2005,7 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
             for (int j = 0; j < G; ++j) {
                 float s0 = 0.0f;
 #pragma unroll
-                for (int v = 0; v < R::kNV; ++v) s0 = Dot<T>::f(kv[u][v], qv[j][v], s0);
+                for (int v = 0; v < R::kNV; ++v) s0 = Dot<float>::f(kv[u][v], qv[j][v], s0);
                 acc[j] = s0;
             }
             float sc_lo, sc_hi;
@@ -2093,7 +2093,7 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
             const int t = t0 + u * NW * VR + sub;
             if (t < nrow) {
 #pragma unroll
-                for (int j = 0; j < G; ++j) Dot<T>::axpy(raw[u], s_sc[j][t], acc[j]);
+                for (int j = 0; j < G; ++j) Dot<float>::axpy(raw[u], s_sc[j][t], acc[j]);
             }
         }
         if (t0 + NW * VR * VU < nrow) load_v(t0 + NW * VR * VU);
@@ -2133,11 +2133,14 @@ __global__ __launch_bounds__(kDenseThreads, (kDenseWaves<T, D, G>)) void k_dense
 // l % 16), a running maximum per head, weights in float32 through a wave-private LDS
 // tile, and the weighted value sums in float32, VL lanes a value row for all heads.
 // The waves' (o, m, l) are combined once, at the end.  The four 32-dim products of a
-// score are summed as a tree and no value sum is a chain of more than 16 terms: against
-// float64 the outputs are 2.2e-7 off at 128K (2.3e-7 for chunks of 1024 rows).  Bound by HBM where a block has
-// many tiles (128K rows, 8 groups of 4: 93 us for 537 MB = 5.8 TB/s, the streaming
-// read's rate; the chunk-at-a-time kernel of k_dense took 100 us), by latency where it
-// has one (16K rows, 4 groups of 7: 10 us, 30 before in 64 chunks of 1024 rows).
+// score are summed as a tree, and a lane's value sums are chains of 16 terms that a
+// flush adds to the wave's sum in LDS (9 flushes for a chunk of 128K rows of 8 groups,
+// about 130 for the longest chunk): against float64 the outputs are 2.2e-7 off at 128K
+// (2.3e-7 for chunks of 1024 rows).  Bound by HBM where a block has many tiles (128K rows,
+// 8 groups of 4: 93 us for 537 MB = 5.8 TB/s, the streaming read's rate; the
+// chunk-at-a-time kernel took 100 us), by latency where it has one (16K rows, 4 groups
+// of 7, the whole call: 16.0 us with K and V in the caches, 35.6 before in 64 chunks of
+// 1024 rows; 20.3 and 43.2 from HBM).
 template <int D, int G>
 __global__ __launch_bounds__(kDenseWaveThreads, 2) void k_dense_wave(StepArgs a, Ws w)
 {
@@ -2745,16 +2748,16 @@ static void dense_wave_g(const StepArgs &a, KernelDesc *k)
     *k = KernelDesc{f, dim3(blocks), dim3(kDenseWaveThreads), 0u, 2};
 }
 
-template <typename T, int D>
+template <int D>
 static void dense_g(const StepArgs &a, KernelDesc *k)
 {
     const unsigned blocks = (unsigned)((int64_t)a.B * a.Hkv * ((a.len + a.dense_rows - 1) / a.dense_rows));
     const void *f;
     switch (a.G) {
-    case 1: f = (const void *)&k_dense<T, D, 1>; break;
-    case 2: f = (const void *)&k_dense<T, D, 2>; break;
-    case 3: case 4: f = (const void *)&k_dense<T, D, 4>; break;
-    default: f = (const void *)&k_dense<T, D, 8>; break;
+    case 1: f = (const void *)&k_dense<D, 1>; break;
+    case 2: f = (const void *)&k_dense<D, 2>; break;
+    case 3: case 4: f = (const void *)&k_dense<D, 4>; break;
+    default: f = (const void *)&k_dense<D, 8>; break;
     }
     *k = KernelDesc{f, dim3(blocks), dim3(kDenseThreads), 0u, 2};
 }
@@ -2777,7 +2780,7 @@ void describe_kernel(int which, int dtype, const StepArgs &a, const Geometry &ge
         return;
     case KERNEL_DENSE:
         if (bf) return d64 ? dense_wave_g<64>(a, k) : dense_wave_g<128>(a, k);
-        return d64 ? dense_g<float, 64>(a, k) : dense_g<float, 128>(a, k);
+        return d64 ? dense_g<64>(a, k) : dense_g<128>(a, k);
     case KERNEL_DENSE_MERGE:
         *k = KernelDesc{d64 ? (const void *)&k_dense_merge<64> : (const void *)&k_dense_merge<128>,
                         dim3((unsigned)(a.B * a.Hq)), dim3(kMergeThreads), 0u, 2};
