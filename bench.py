@@ -440,8 +440,10 @@ def step_stats(ms) -> dict:
 
 
 def kernel_source_digest() -> str:
+    """Digest of the files that decide the profiled launches: their code and geometry."""
     h = hashlib.sha256()
-    for name in ("retopk_kernels.hip", "retopk_device.h"):
+    for name in ("retopk_kernels.hip", "retopk_device.h", "retopk_internal.h", "retopk_plan.h",
+                 "retopk_api.hip"):
         with open(os.path.join(ROOT, "paper_2607_27692_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
@@ -973,6 +975,7 @@ SYMBOLS = {  # kernel symbol prefix -> name used by the library's own profiling
     "void retopk::k_dense_merge<": "dense_merge",
     "void retopk::k_pf_scan<": "prefill_score",
     "void retopk::k_pf_bound<": "retopk_filter",
+    "retopk::k_pf_raise(": "retopk_filter",
     "void retopk::k_pf_select<": "retopk_final",
     "void retopk::k_scan_list<": "retopk_scan",
 }
@@ -998,10 +1001,10 @@ def _passes(names, w, steps, warmup):
     """Splits the library's dispatches (in dispatch order) into the bench's
     passes.  Every pass starts on a fresh handle whose prefill issues, per launch
     of prompt-tail positions, prefill_score, filter, prefill_score, final (bounds
-    and lists) or prefill_score, final (score rows), or the older prefill_score,
-    filter, final triple (a scan, filter, final triple per position for f32); a
-    decode step that selects
-    issues sim, score, filter, final, any other step or an Exact Top-K step
+    and lists), behind which filter, prefill_score, final may follow (lists
+    collected again), or prefill_score, final (score rows), or the older
+    prefill_score, filter, final triple (a scan, filter, final triple per position
+    for f32); a decode step that selects issues sim, score, filter, final, any other step or an Exact Top-K step
     scan, filter, final, and a full-attention step dense_chunk, dense_merge.
     The warm-up runs one step of each kind per warm-up step, then one handle
     runs the timed prefill alone; after the six passes come the two warm-cache
@@ -1018,7 +1021,8 @@ def _passes(names, w, steps, warmup):
     out, i = [], 0
     pf_units = (["prefill_score", "retopk_filter", "prefill_score", "retopk_final"],
                 ["prefill_score", "retopk_filter", "retopk_final"],
-                ["prefill_score", "retopk_final"])
+                ["prefill_score", "retopk_final"],
+                ["retopk_filter", "prefill_score", "retopk_final"])
     prefill = None
     pf = None        # one prefill's launches: every handle's prefill is the same
     for label, n_units in plan:
@@ -1026,7 +1030,7 @@ def _passes(names, w, steps, warmup):
         if names[i] == "prefill_score":
             if pf is None:     # the first handle's prefill is followed by steps
                 pf, j = [], i
-                while names[j] == "prefill_score":
+                while names[j] in ("prefill_score", "retopk_filter"):
                     unit = next(u for u in pf_units if names[j:j + len(u)] == u)
                     pf += unit
                     j += len(unit)

@@ -2,9 +2,11 @@
 retained mass, cosine) on hand-made inputs, the split of a profile into passes,
 the one-GPU guard and the traffic lookup."""
 import os
+import shutil
 import sys
 
 import numpy as np
+import pytest
 
 sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
 import bench  # noqa: E402
@@ -95,6 +97,51 @@ def test_traffic_is_reported_only_for_the_profiled_source(monkeypatch):
     monkeypatch.setattr(bench, "kernel_source_digest", lambda: "0" * 64)
     assert bench.traffic_per_launch("retopk_score", "128k") is None
     assert bench.traffic_per_launch("no_such_kernel", "128k") is None
+
+
+@pytest.mark.parametrize("name", ["retopk_kernels.hip", "retopk_device.h", "retopk_internal.h",
+                                  "retopk_plan.h", "retopk_api.hip"])
+def test_source_digest_covers_kernels_and_geometry(name, tmp_path, monkeypatch):
+    """Any file that decides a profiled launch, its code or its grid, changes the digest."""
+    csrc = os.path.join("paper_2607_27692_amd", "csrc")
+    shutil.copytree(os.path.join(bench.ROOT, csrc), tmp_path / csrc)
+    before = bench.kernel_source_digest()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.kernel_source_digest() == before
+    with open(tmp_path / csrc / name, "a") as f:
+        f.write("// changed\n")
+    assert bench.kernel_source_digest() != before
+
+
+def test_prefill_passes_with_lists_collected_again():
+    """A prefill of two launches with lists, one of which overflowed and ran again, and a
+    prompt with score rows: the bench's passes are found behind both."""
+    from paper_2607_27692_amd.inputs import WORKLOADS
+    w = WORKLOADS["128k"]
+    lists = ["prefill_score", "retopk_filter", "prefill_score", "retopk_final"]
+    again = ["retopk_filter", "prefill_score", "retopk_final"]
+    steps = 2
+    step = ["retopk_sim", "retopk_score", "retopk_filter", "retopk_final"]
+    exact = ["retopk_scan", "retopk_filter", "retopk_final"]
+    full = ["dense_chunk", "dense_merge"]
+    for pf in (lists * 2 + again, ["prefill_score", "retopk_final"] * 3):
+        names = pf + step + exact + full + pf
+        for kind in (step, exact, full, step, exact, full, step, exact, step):
+            names += pf + kind * steps
+        passes, prefill = bench._passes(names, w, steps, 1)
+        assert names[prefill[0]:prefill[1]] == pf
+        by = {p[0]: names[p[1]:p[2]] for p in passes}
+        assert by["full timed"] == full * steps and by["step kinds"] == step * steps
+
+
+def test_trace_symbols_name_every_prefill_build():
+    for d in (64, 128):
+        for mode in (0, 1, 2, 7):
+            assert bench._lib_name(f"void retopk::k_pf_scan<{d}, {mode}>(retopk::PfArgs)") == "prefill_score"
+        assert bench._lib_name(f"void retopk::k_pf_select<{d}, false>(retopk::PfArgs)") == "retopk_final"
+        assert bench._lib_name(f"void retopk::k_dense<{d}, 4>(retopk::StepArgs, retopk::Ws)") == "dense_chunk"
+    assert bench._lib_name("void retopk::k_pf_bound<16>(retopk::PfArgs)") == "retopk_filter"
+    assert bench._lib_name("retopk::k_pf_raise(retopk::PfArgs)") == "retopk_filter"
 
 
 def test_trace_symbols_name_every_score_build():
