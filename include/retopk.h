@@ -134,12 +134,13 @@ retopk_status retopk_destroy(retopk_handle h);
  * decode-step counter.  Queries whose slot a later one overwrites (n > C) only
  * advance the insertion count.  bf16 handles score many positions of every head
  * per launch on the matrix cores (kernel id 7) with up to about 270 MB of device
- * memory, and return after the stream has finished that work, which a stream under
- * capture refuses (RETOPK_ERR_HIP before anything is queued).  One such workspace a
- * device is kept for later prefills of any handle until the device's last handle is
- * destroyed; calls that overlap on other threads allocate their own.  When the memory
- * is not available, and for f32 or a single query, the queries run one position at a
- * time through the decode step's exact path, asynchronously. */
+ * memory (and 8 bytes a query and head), and return after the stream has finished
+ * that work, which a stream under capture refuses (RETOPK_ERR_HIP before anything is
+ * queued).  One such workspace a device is kept for later prefills of any handle
+ * until the device's last handle is destroyed; calls that overlap on other threads
+ * allocate their own.  When the memory is not available, and for f32 or a single
+ * query, the queries run one position at a time through the decode step's exact
+ * path, asynchronously. */
 retopk_status retopk_prefill_init(retopk_handle h, const void *q_tail, int32_t n,
                                   const void *k, const void *v, int64_t prefill_len,
                                   void *stream);
@@ -244,8 +245,9 @@ retopk_status retopk_set_state(retopk_handle h, const float *qbar, const int32_t
  *   6 dense_merge    full_attention: merge of the chunks
  *   7 prefill_score  bf16 prefill: scores of many prompt-tail positions of every
  *                    head (matrix cores), for the bounds of their K-th
- *                    largest and for the entries above them; the bounds count
- *                    as retopk_filter, the selection as retopk_final */
+ *                    largest and for the entries above them (once more for lists
+ *                    that overflowed), or for score rows; the bounds count as
+ *                    retopk_filter, the selection as retopk_final */
 retopk_status retopk_profile(retopk_handle h, int32_t enable);
 retopk_status retopk_profile_read(retopk_handle h, int32_t n_kernels, uint64_t *launches,
                                   double *total_ms);

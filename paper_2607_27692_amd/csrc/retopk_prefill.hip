@@ -69,12 +69,12 @@ __device__ __forceinline__ float fmax_nan(float x, float y) { return __builtin_e
 // core.  Blocks on the same chunk run on one XCD (equal blockIdx % 8) and share
 // its keys through that L2.
 // For 256 positions of 32 heads at 128K and K = 512 (1024 queries a group, 275 GFLOP
-// over all keys): BOUND over half the keys 130 us, COLLECT 380 us, of which about
+// over all keys): BOUND over half the keys 131 us, COLLECT 387 us, of which about
 // 100 us append 1100 entries a virtual head (F = 1, a tighter bound from every key,
 // costs another 130 us of BOUND; F = 4 twice the appends).  The matrix cores are busy
-// 45 % and 30 % of that; a build without LDS staging (each wave loading its own
-// tiles) took 292 and 442 us, and the earlier kernel that stored every score and
-// counted it in LDS histograms 2500 us for the same positions, its filter 1100 us.
+// 46 % and 32 % of that; a build without LDS staging (each wave loading its own
+// tiles) took 292 and 442 us, and the kernel that stored every score and counted it
+// in LDS histograms 2500 us for the same positions, its filter 1100 us.
 template <int D, int MODE>
 __global__ __launch_bounds__(kPfThreads, 2) void k_pf_scan(PfArgs a)
 {
