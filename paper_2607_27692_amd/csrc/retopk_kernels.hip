@@ -2699,6 +2699,16 @@ static void score_desc(const StepArgs &a, const Geometry &geo, KernelDesc *k)
     }
 }
 
+// The kernels of a bf16 d = 128 decode step, emitted side by side (with k_filter, which
+// comes first): together they are as large as the 64 KB instruction cache, and where
+// other kernels lay between them the same code took 0.1 to 0.25 us longer a step, in the
+// gaps between the launches (128K rows, 32/8 heads: 36.5 us apart, 36.3 side by side;
+// 28/4 heads 34.17 and 34.07).
+template __global__ void k_score<uint16_t, 128, 8, true>(StepArgs, Ws, Geometry);
+template __global__ void k_sim<uint16_t, 128>(StepArgs, Ws);
+template __global__ void k_final<uint16_t, 128, 8, 8>(StepArgs, Ws);
+template __global__ void k_score<uint16_t, 128, 4, true>(StepArgs, Ws, Geometry);
+
 // k_final's geometry for a decode launch: slices per head so that the launch has
 // about 256 blocks (one per CU; each block takes most of a CU's LDS), and 16
 // entries per thread where a head's candidate cap is well past 4096 entries.
