@@ -346,7 +346,8 @@ struct PfWorkspace {
 // Runs of the lists that overflowed, each under a bound that the one before left, before
 // their positions take score rows.  Of keys without ties a run leaves about an eighth of
 // what overflowed; of equal scores it keeps the lower indices, and the list holds what
-// came first from every key chunk, so that a few runs reach the K lowest.
+// came first from every key chunk, so that a few runs reach the K lowest.  No input tried
+// needed a fourth; score rows bound the worst.
 constexpr int kPfReruns = 3;
 
 // Batched prefill initialisation (bf16): positions u_first .. n-1 of q_tail in
